@@ -57,7 +57,8 @@ struct RunArgs {
     float *work;        // segment partial sums [n_seg * work_ld], then window partials
                         // [n_wpart * H * work_ld]
     int32_t work_ld;    // row stride of `work` (N rounded up to 4)
-    int32_t vec_ok;     // 16-byte chunks usable for B and C
+    int32_t vec_ok;     // rows hold at least one 16-byte chunk of B (4 f32, 8 16-bit elements)
+    int32_t win_vec;    // windows: rows of B and C are whole, aligned 16-byte chunks
     int32_t np;         // columns per panel of the vector / segment kernels
     int32_t n_panels;
     int32_t lpr_log2;   // log2(lanes per entry group) for the vector / segment kernels
@@ -66,8 +67,8 @@ struct RunArgs {
     int32_t win_np;     // columns per window panel: 128, or 64 / 32 for 16-bit B with N <= 64
     int32_t win_lpr_log2;
     int32_t cold_aux;   // buffer-load policy bits for non-hot B rows; -1: plain loads for all
-    uint32_t b_rec;     // bytes of B reachable through a buffer resource (its span);
-                        // 0 when B spans 4 GiB or more (predicated plain loads)
+    uint32_t b_rec;     // bytes of B reachable through a buffer resource (its span); 0 when B
+                        // spans 4 GiB or more or its chunks are not aligned to 4 bytes (plain loads)
     int32_t pipeline;   // vector kernel variant: 0 row by row, 1 row-pipelined, 2 short rows packed,
                         // 3 rows packed by size class
     // co-scheduled execution
@@ -108,11 +109,11 @@ struct BatchGrids {
 };
 // Persistent batched launches over a device table (header + entries).
 hipError_t launch_batch(const BatchHeader *hdr, const BatchEntry *tab, int32_t val_t, int32_t b_t,
-                        int32_t tile_t, int vec_ok, int cpl, int var, const BatchGrids &grids,
-                        hipStream_t s);
+                        int32_t tile_t, int vec_ok, int win_vec, int cpl, int var,
+                        const BatchGrids &grids, hipStream_t s);
 // Resident workgroups per CU of each batched kernel of this variant.
-hipError_t batch_occupancy(int32_t val_t, int32_t b_t, int32_t tile_t, int vec_ok, int cpl,
-                           int var, BatchGrids *per_cu);
+hipError_t batch_occupancy(int32_t val_t, int32_t b_t, int32_t tile_t, int vec_ok, int win_vec,
+                           int cpl, int var, BatchGrids *per_cu);
 
 // dtype codes as in spmm.h
 hipError_t launch_segment(const DevPlan &P, int32_t val_t, int32_t b_t, const RunArgs &a,

@@ -117,7 +117,7 @@ template <int VT, int BT, int TT, int MB>
 static hipError_t mp_mb(const DevPlan &P, const RunArgs &a, hipStream_t s) {
     constexpr int EV = BT == DT_F32 ? 4 : 8;
     const dim3 grid((unsigned)(a.wpart_blocks + a.win_blocks)), block(256);
-    if (!a.vec_ok) {
+    if (!a.win_vec) {
         launch_kernel((mfma_path_kernel<VT, BT, TT, MB, 1, 2, 128>), grid, block, 0, s, P, a);
     } else if constexpr (BT == DT_F32) {
         launch_kernel((mfma_path_kernel<VT, BT, TT, MB, EV, 1, 128>), grid, block, 0, s, P, a);
@@ -180,7 +180,7 @@ static hipError_t og_types(const DevPlan &P, const RunArgs &a, hipStream_t s) {
 
 bool one_grid_supported(int32_t b_t, const RunArgs &a) {
     const int ev = b_t == DT_F32 ? 4 : 8;
-    return a.vec_ok && (a.np + ev - 1) / ev <= 64 && (a.pipeline == 2 || a.pipeline == 3) &&
+    return a.win_vec && (a.np + ev - 1) / ev <= 64 && (a.pipeline == 2 || a.pipeline == 3) &&
            a.win_np == 128;
 }
 

@@ -39,6 +39,28 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+// 16 bytes at element alignment: a row of N columns with any leading dimension
+// starts anywhere, and gfx950 reads and writes 16 bytes at such an address in
+// one instruction (two cache lines where it straddles them)
+typedef float f32x4e __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned int u32x4e __attribute__((ext_vector_type(4), aligned(2)));
+
+// First column of chunk q of a panel of ncols >= E columns: a last chunk that
+// would run past the panel starts at its last E columns instead, so every
+// chunk is whole and in bounds; the columns it shares with the chunk before it
+// are computed twice from the same operands in the same order, so both lanes
+// store the same values.
+template <int E>
+__device__ __forceinline__ int chunk_col(int q, int ncols) {
+    return E == 1 ? q : min(q * E, ncols - E);
+}
+
+// First column of panel p of width np: the last panel is widened to the left
+// to hold a whole chunk.
+template <int E>
+__device__ __forceinline__ int panel_col(int p, int np, int n) {
+    return E == 1 ? p * np : min(p * np, n - E);
+}
 
 __device__ __forceinline__ float bf16_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
 __device__ __forceinline__ float f16_to_f32(uint32_t h) {
@@ -62,7 +84,6 @@ __device__ __forceinline__ float load_val(const void *base, int idx) {
     }
 }
 
-// E consecutive elements of B (as float) starting at element offset `off`.
 // NT selects the non-temporal cache policy (the line is streamed through L2
 // and is the first to be evicted), used for B rows outside the hot set.
 template <bool NT, class T>
@@ -71,33 +92,17 @@ __device__ __forceinline__ T ld(const T *p) {
     else return *p;
 }
 
-template <int BT, int E, bool NT = false>
-__device__ __forceinline__ void load_chunk(const void *B, int64_t off, float (&v)[E]) {
-    if constexpr (E == 1) {
-        if constexpr (BT == DT_F32)
-            v[0] = ld<NT>(static_cast<const float *>(B) + off);
-        else if constexpr (BT == DT_BF16)
-            v[0] = bf16_to_f32(ld<NT>(static_cast<const unsigned short *>(B) + off));
-        else
-            v[0] = f16_to_f32(ld<NT>(static_cast<const unsigned short *>(B) + off));
-    } else if constexpr (BT == DT_F32) {
-        static_assert(E == 4, "f32 chunks are 4 wide");
-        f32x4 x = ld<NT>(reinterpret_cast<const f32x4 *>(static_cast<const float *>(B) + off));
-        v[0] = x[0]; v[1] = x[1]; v[2] = x[2]; v[3] = x[3];
-    } else {
-        static_assert(E == 8, "16-bit chunks are 8 wide");
-        u32x4 x = ld<NT>(reinterpret_cast<const u32x4 *>(static_cast<const unsigned short *>(B) + off));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if constexpr (BT == DT_BF16) {
-                v[2 * i] = __uint_as_float(x[i] << 16);
-                v[2 * i + 1] = __uint_as_float(x[i] & 0xFFFF0000u);
-            } else {
-                v[2 * i] = f16_to_f32(x[i] & 0xFFFFu);
-                v[2 * i + 1] = f16_to_f32(x[i] >> 16);
-            }
-        }
-    }
+template <bool NT>
+__device__ __forceinline__ f32x4 ld16(const float *p) {
+    const f32x4e *q = reinterpret_cast<const f32x4e *>(p);
+    if constexpr (NT) return __builtin_nontemporal_load(q);
+    else return *q;
+}
+template <bool NT>
+__device__ __forceinline__ u32x4 ld16(const unsigned short *p) {
+    const u32x4e *q = reinterpret_cast<const u32x4e *>(p);
+    if constexpr (NT) return __builtin_nontemporal_load(q);
+    else return *q;
 }
 
 // A gathered chunk kept in its stored form until it is consumed, so that 16-bit
@@ -117,9 +122,9 @@ __device__ __forceinline__ void load_raw(const void *B, int64_t off, Raw<BT, E> 
         else
             r.x = ld<NT>(static_cast<const unsigned short *>(B) + off);
     } else if constexpr (BT == DT_F32) {
-        r.x = ld<NT>(reinterpret_cast<const f32x4 *>(static_cast<const float *>(B) + off));
+        r.x = ld16<NT>(static_cast<const float *>(B) + off);
     } else {
-        r.x = ld<NT>(reinterpret_cast<const u32x4 *>(static_cast<const unsigned short *>(B) + off));
+        r.x = ld16<NT>(static_cast<const unsigned short *>(B) + off);
     }
 }
 
@@ -284,8 +289,8 @@ __device__ __forceinline__ void store_chunk(float *C, int64_t off, const float (
     } else {
 #pragma unroll
         for (int i = 0; i < E; i += 4) {
-            f32x4 x = {v[i], v[i + 1], v[i + 2], v[i + 3]};
-            __builtin_nontemporal_store(x, reinterpret_cast<f32x4 *>(C + off + i));
+            f32x4e x = {v[i], v[i + 1], v[i + 2], v[i + 3]};
+            __builtin_nontemporal_store(x, reinterpret_cast<f32x4e *>(C + off + i));
         }
     }
 }
@@ -297,7 +302,7 @@ __device__ __forceinline__ void load_f32_chunk(const float *W, int64_t off, floa
     } else {
 #pragma unroll
         for (int i = 0; i < E; i += 4) {
-            f32x4 x = *reinterpret_cast<const f32x4 *>(W + off + i);
+            f32x4 x = *reinterpret_cast<const f32x4e *>(W + off + i);
             v[i] = x[0]; v[i + 1] = x[1]; v[i + 2] = x[2]; v[i + 3] = x[3];
         }
     }
@@ -409,15 +414,16 @@ __device__ __forceinline__ void gather_fma(const int (&col)[U], const float (&v)
                 // resource (a branch makes the compiler wait for each load
                 // before issuing the next): a masked entry or a chunk outside
                 // the panel loads at offset brec, out of the buffer's range,
-                // which returns zeros without a memory access.  B spanning
-                // 4 GiB or more takes predicated plain loads.
+                // which returns zeros without a memory access.  Without one (B
+                // spanning 4 GiB or more, or 16-bit rows not aligned to 4
+                // bytes) every load is a plain one, a masked entry's from the
+                // row its column names (a row of B: its clamped entry's, or
+                // row 0), and its value is not used.
                 (void)cold_aux;
                 if (brec != 0) {
                     load_raw_buf<BT, E>(rs, ok && cok[c] ? (uint32_t)(boff * SB) : brec, b[u][c]);
-                } else if (ok && cok[c]) {
-                    load_raw<BT, E, false>(B, boff, b[u][c]);
                 } else {
-                    zero_raw<BT, E>(b[u][c]);
+                    load_raw<BT, E, false>(B, boff, b[u][c]);
                 }
             }
         }
@@ -452,7 +458,7 @@ __device__ __forceinline__ void chunk_layout(int ncol0, int ncols, const Lanes &
     for (int c = 0; c < CPL; ++c) {
         const int q = c * L.lpr + L.li;
         cok[c] = q * E < ncols;
-        coff[c] = ncol0 + (cok[c] ? (int64_t)q * E : 0);  // a valid chunk when outside the panel
+        coff[c] = ncol0 + (cok[c] ? chunk_col<E>(q, ncols) : 0);  // a valid chunk when outside the panel
     }
 }
 
@@ -563,7 +569,7 @@ __device__ __forceinline__ void sum_partials(const float *__restrict__ work, int
     for (int c = 0; c < CPL; ++c) {
         const int q = c * L.lpr + L.li;
         if (q * E >= ncols) continue;
-        const int64_t off = ncol0 + (int64_t)q * E;
+        const int64_t off = ncol0 + chunk_col<E>(q, ncols);
         if constexpr (DEV) {
             (void)work;
             ld_dev_chunk<E>(rs, (int64_t)sid * ld + off, acc[c]);
@@ -598,7 +604,7 @@ __device__ __forceinline__ void store_row(float *C, int64_t row_off, int ncol0, 
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
         const int q = c * L.lpr + L.li;
-        if (q * E < ncols) store_chunk<E>(C, row_off + ncol0 + (int64_t)q * E, acc[c]);
+        if (q * E < ncols) store_chunk<E>(C, row_off + ncol0 + chunk_col<E>(q, ncols), acc[c]);
     }
 }
 
@@ -726,7 +732,7 @@ template <int VT, int BT, int E, int CPL, bool POL, bool FUSED = false>
 __device__ __forceinline__ void segment_item(const DevPlan &P, const RunArgs &a, int wid) {
     const int panel = wid / P.n_seg, li = wid - panel * P.n_seg;
     const int sid = P.seg_order ? P.seg_order[li] : li;  // the partial's slot
-    const int ncol0 = panel * a.np, ncols = min(a.np, P.n - ncol0);
+    const int ncol0 = panel_col<E>(panel, a.np, P.n), ncols = min(a.np, P.n - ncol0);
     const Lanes L(a.lpr_log2);
     float acc[CPL][E];
 #pragma unroll
@@ -742,16 +748,17 @@ __device__ __forceinline__ void segment_item(const DevPlan &P, const RunArgs &a,
         for (int c = 0; c < CPL; ++c) {
             const int q = c * L.lpr + L.li;
             if (q * E < ncols) {
-                float *dst = a.work + (int64_t)sid * a.work_ld + ncol0 + (int64_t)q * E;
+                const int64_t off = (int64_t)sid * a.work_ld + ncol0 + chunk_col<E>(q, ncols);
+                float *dst = a.work + off;
                 if constexpr (FUSED) {
-                    st_dev_chunk<E>(ws_resource(a), (int64_t)sid * a.work_ld + ncol0 + (int64_t)q * E, acc[c]);
+                    st_dev_chunk<E>(ws_resource(a), off, acc[c]);
                 } else if constexpr (E == 1) {
                     dst[0] = acc[c][0];
                 } else {
 #pragma unroll
                     for (int i = 0; i < E; i += 4)
-                        *reinterpret_cast<f32x4 *>(dst + i) =
-                            f32x4{acc[c][i], acc[c][i + 1], acc[c][i + 2], acc[c][i + 3]};
+                        *reinterpret_cast<f32x4e *>(dst + i) =
+                            f32x4e{acc[c][i], acc[c][i + 1], acc[c][i + 2], acc[c][i + 3]};
                 }
             }
         }
@@ -772,7 +779,8 @@ __device__ __forceinline__ void segment_item(const DevPlan &P, const RunArgs &a,
             }
         } else {
             const int dep = P.win_dep[w];
-            for (int q = ncol0 / a.win_np; q <= (ncol0 + ncols - 1) / a.win_np; ++q)
+            // (the panel's own columns, without those it was widened by: win_target)
+            for (int q = panel * a.np / a.win_np; q <= (ncol0 + ncols - 1) / a.win_np; ++q)
                 if (wave_arrive(win_counter(P, a, q, dep), win_target(P, a, w, q)))
                     window_combine(P, a, w, q, dep, threadIdx.x & 63, 64);
         }
@@ -785,7 +793,7 @@ __device__ __forceinline__ void segment_item(const DevPlan &P, const RunArgs &a,
 template <int VT, int BT, int E, int CPL, bool FUSED = false>
 __device__ __forceinline__ void vector_item(const DevPlan &P, const RunArgs &a, int wid) {
     const int panel = wid / P.n_vitems, item = wid - panel * P.n_vitems;
-    const int ncol0 = panel * a.np, ncols = min(a.np, P.n - ncol0);
+    const int ncol0 = panel_col<E>(panel, a.np, P.n), ncols = min(a.np, P.n - ncol0);
     const Lanes L(a.lpr_log2);
     int sid = P.vitem_seg[item];
     const int i0 = P.vitem_ptr[item], i1 = P.vitem_ptr[item + 1];
@@ -820,7 +828,7 @@ template <int VT, int BT, int E, int CPL, bool FUSED = false>
 __device__ __forceinline__ void vector_item_pipelined(const DevPlan &P, const RunArgs &a, int wid) {
     constexpr int U = unroll_of<E, CPL>();
     const int panel = wid / P.n_vitems, item = wid - panel * P.n_vitems;
-    const int ncol0 = panel * a.np, ncols = min(a.np, P.n - ncol0);
+    const int ncol0 = panel_col<E>(panel, a.np, P.n), ncols = min(a.np, P.n - ncol0);
     const Lanes L(a.lpr_log2);
     const int step = L.groups * U;
     const __amdgpu_buffer_rsrc_t rs = b_resource(a.B, a.b_rec);
@@ -928,7 +936,7 @@ __device__ __forceinline__ void vector_item_packed(const DevPlan &P, const RunAr
     constexpr int U = UL;
     constexpr int SHORT = 2 * unroll_of<E, CPL>();
     const int panel = wid / P.n_vitems, item = wid - panel * P.n_vitems;
-    const int ncol0 = panel * a.np, ncols = min(a.np, P.n - ncol0);
+    const int ncol0 = panel_col<E>(panel, a.np, P.n), ncols = min(a.np, P.n - ncol0);
     const Lanes L(a.lpr_log2);
     const int lane = threadIdx.x & 63;
     int sid = P.vitem_seg[item];
@@ -965,7 +973,8 @@ __device__ __forceinline__ void vector_item_packed(const DevPlan &P, const RunAr
 #pragma unroll
                     for (int c = 0; c < CPL; ++c) {
                         const int q = c * L.lpr + L.li;
-                        if (q * E < ncols) store_chunk<E>(a.C, (int64_t)r * a.ldc + ncol0 + (int64_t)q * E, acc[c]);
+                        if (q * E < ncols)
+                            store_chunk<E>(a.C, (int64_t)r * a.ldc + ncol0 + chunk_col<E>(q, ncols), acc[c]);
                     }
                 }
                 j += k;
@@ -1026,7 +1035,7 @@ template <int VT, int BT, int E, int CPL, bool FUSED = false, int UL = unroll_of
 __device__ __forceinline__ void vector_item_classed(const DevPlan &P, const RunArgs &a, int wid) {
     constexpr int U = UL;
     const int panel = wid / P.n_vitems, item = wid - panel * P.n_vitems;
-    const int ncol0 = panel * a.np, ncols = min(a.np, P.n - ncol0);
+    const int ncol0 = panel_col<E>(panel, a.np, P.n), ncols = min(a.np, P.n - ncol0);
     const Lanes L(a.lpr_log2);
     const int lane = threadIdx.x & 63;
     const __amdgpu_buffer_rsrc_t rs = b_resource(a.B, a.b_rec);
@@ -1129,7 +1138,7 @@ __device__ __forceinline__ void vector_item_classed(const DevPlan &P, const RunA
 #pragma unroll
             for (int c = 0; c < CPL; ++c) {
                 const int q = c * L.lpr + L.li;
-                if (q * E < ncols) store_chunk<E>(a.C, (int64_t)my_r * a.ldc + ncol0 + (int64_t)q * E, acc[c]);
+                if (q * E < ncols) store_chunk<E>(a.C, (int64_t)my_r * a.ldc + ncol0 + chunk_col<E>(q, ncols), acc[c]);
             }
         }
         i += k;
@@ -1259,7 +1268,7 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
     const int j_item = item / a.win_panels, panel = item - j_item * a.win_panels;
     const int wi = partial ? P.wpart_win[j_item] : (P.win_order ? P.win_order[j_item] : j_item);
     const int ncol0 = panel * NPW, ncols = min(NPW, P.n - ncol0);
-    const bool full = a.vec_ok && ncols == NPW;  // every staging chunk is whole
+    const bool full = a.win_vec && ncols == NPW;  // every staging chunk is whole
     const int tid = threadIdx.x, wave = wave_id(), lane = tid & 63;
     const int g = lane >> 4, l16 = lane & 15;
     const int t0 = partial ? P.wpart_t0[j_item] : P.win_tile_ptr[wi];
@@ -1409,7 +1418,7 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
                     uint32_t w[4] = {0u, 0u, 0u, 0u};
                     const int valid = min(8, ncols - cg * 8);
                     if (colr[it] >= 0 && valid > 0)
-                        stage_b8<BT, TT>(a.B, (int64_t)colr[it] * a.ldb + ncol0 + cg * 8, valid, a.vec_ok, w);
+                        stage_b8<BT, TT>(a.B, (int64_t)colr[it] * a.ldb + ncol0 + cg * 8, valid, a.win_vec, w);
                     *reinterpret_cast<u32x4 *>(&Bs[it * 2048 + tid * 8]) = u32x4{w[0], w[1], w[2], w[3]};
                 }
             }
@@ -1434,7 +1443,7 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
                         w[q][2] = ok ? (f32_to_bf16_bits(x1[0]) | (f32_to_bf16_bits(x1[1]) << 16)) : 0u;
                         w[q][3] = ok ? (f32_to_bf16_bits(x1[2]) | (f32_to_bf16_bits(x1[3]) << 16)) : 0u;
                     } else if (colr[it] >= 0 && valid > 0) {
-                        stage_b8<BT, TT>(a.B, (int64_t)colr[it] * a.ldb + ncol0 + cg * 8, valid, a.vec_ok,
+                        stage_b8<BT, TT>(a.B, (int64_t)colr[it] * a.ldb + ncol0 + cg * 8, valid, a.win_vec,
                                          w[q]);
                     }
                 }

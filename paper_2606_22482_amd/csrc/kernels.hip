@@ -184,7 +184,7 @@ static hipError_t win_dispatch(const DevPlan &P, const RunArgs &a, hipStream_t s
     } while (0)
 #define SPMM_WIN(MB)                                                                                 \
     do {                                                                                             \
-        if (!a.vec_ok) {                                                                             \
+        if (!a.win_vec) {                                                                            \
             if (partial)                                                                             \
                 launch_kernel((window_partial_kernel<VT, BT, TT, MB, 1, 2, 128>), grid, block, 0, s, P, a); \
             else                                                                                     \
@@ -243,7 +243,8 @@ hipError_t launch_window_partial(const DevPlan &P, int32_t vt, int32_t bt, int32
     return window_any(P, vt, bt, tt, a, s, true);
 }
 
-template <int VT, int BT, int TT, int E, int CPL, int VAR>
+// E, CPL: chunks of the segment and vector kernels; EW, CW: of the windows'.
+template <int VT, int BT, int TT, int E, int CPL, int EW, int CW, int VAR>
 static hipError_t batch_variant(const BatchHeader *hdr, const BatchEntry *tab, const BatchGrids &g,
                                 hipStream_t s, BatchGrids *occ) {
     if (occ) {
@@ -256,61 +257,66 @@ static hipError_t batch_variant(const BatchHeader *hdr, const BatchEntry *tab, c
         if (e != hipSuccess) return e;
         occ->vec = (unsigned)o;
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &o, batch_window_kernel<VT, BT, TT, E, CPL, false>, 256, 0);
+            &o, batch_window_kernel<VT, BT, TT, EW, CW, false>, 256, 0);
         occ->win = (unsigned)o;
         return e;
     }
     // phase 1: partial sums (segments, window tile chunks); phase 2: owners
     hipLaunchKernelGGL((batch_segment_kernel<VT, BT, E, CPL, VAR == 0>), dim3(g.seg), dim3(256), 0, s, hdr, tab);
-    hipLaunchKernelGGL((batch_window_kernel<VT, BT, TT, E, CPL, true>), dim3(g.win), dim3(256), 0, s,
+    hipLaunchKernelGGL((batch_window_kernel<VT, BT, TT, EW, CW, true>), dim3(g.win), dim3(256), 0, s,
                        hdr, tab);
     hipLaunchKernelGGL((batch_vector_kernel<VT, BT, E, CPL, VAR>), dim3(g.vec), dim3(256), 0, s, hdr, tab);
-    hipLaunchKernelGGL((batch_window_kernel<VT, BT, TT, E, CPL, false>), dim3(g.win), dim3(256), 0,
+    hipLaunchKernelGGL((batch_window_kernel<VT, BT, TT, EW, CW, false>), dim3(g.win), dim3(256), 0,
                        s, hdr, tab);
     return hipGetLastError();
 }
 
 template <int VT, int BT, int TT, int VAR>
 static hipError_t batch_types_var(const BatchHeader *hdr, const BatchEntry *tab, int vec_ok,
-                                  int cpl, const BatchGrids &g, hipStream_t s, BatchGrids *occ) {
+                                  int win_vec, int cpl, const BatchGrids &g, hipStream_t s,
+                                  BatchGrids *occ) {
     constexpr int EV = BT == DT_F32 ? 4 : 8;
-    if (!vec_ok) return batch_variant<VT, BT, TT, 1, 2, VAR>(hdr, tab, g, s, occ);
-    if (cpl == 1) return batch_variant<VT, BT, TT, EV, 1, VAR>(hdr, tab, g, s, occ);
-    return batch_variant<VT, BT, TT, EV, 2, VAR>(hdr, tab, g, s, occ);
+    if (!vec_ok) return batch_variant<VT, BT, TT, 1, 2, 1, 2, VAR>(hdr, tab, g, s, occ);
+    if (!win_vec) {
+        if (cpl == 1) return batch_variant<VT, BT, TT, EV, 1, 1, 2, VAR>(hdr, tab, g, s, occ);
+        return batch_variant<VT, BT, TT, EV, 2, 1, 2, VAR>(hdr, tab, g, s, occ);
+    }
+    if (cpl == 1) return batch_variant<VT, BT, TT, EV, 1, EV, 1, VAR>(hdr, tab, g, s, occ);
+    return batch_variant<VT, BT, TT, EV, 2, EV, 2, VAR>(hdr, tab, g, s, occ);
 }
 
 template <int VT, int BT, int TT>
-static hipError_t batch_types(const BatchHeader *hdr, const BatchEntry *tab, int vec_ok, int cpl,
-                              int var, const BatchGrids &g, hipStream_t s, BatchGrids *occ) {
-    if (var == 3) return batch_types_var<VT, BT, TT, 3>(hdr, tab, vec_ok, cpl, g, s, occ);
-    if (var == 2) return batch_types_var<VT, BT, TT, 2>(hdr, tab, vec_ok, cpl, g, s, occ);
-    if (var == 1) return batch_types_var<VT, BT, TT, 1>(hdr, tab, vec_ok, cpl, g, s, occ);
-    return batch_types_var<VT, BT, TT, 0>(hdr, tab, vec_ok, cpl, g, s, occ);
+static hipError_t batch_types(const BatchHeader *hdr, const BatchEntry *tab, int vec_ok, int win_vec,
+                              int cpl, int var, const BatchGrids &g, hipStream_t s, BatchGrids *occ) {
+    if (var == 3) return batch_types_var<VT, BT, TT, 3>(hdr, tab, vec_ok, win_vec, cpl, g, s, occ);
+    if (var == 2) return batch_types_var<VT, BT, TT, 2>(hdr, tab, vec_ok, win_vec, cpl, g, s, occ);
+    if (var == 1) return batch_types_var<VT, BT, TT, 1>(hdr, tab, vec_ok, win_vec, cpl, g, s, occ);
+    return batch_types_var<VT, BT, TT, 0>(hdr, tab, vec_ok, win_vec, cpl, g, s, occ);
 }
 
 static hipError_t batch_any(const BatchHeader *hdr, const BatchEntry *tab, int32_t vt, int32_t bt,
-                            int32_t tt, int vec_ok, int cpl, int var, const BatchGrids &g,
+                            int32_t tt, int vec_ok, int win_vec, int cpl, int var, const BatchGrids &g,
                             hipStream_t s, BatchGrids *occ) {
     if (vt == DT_F32 && bt == DT_F32 && tt == DT_BF16)
-        return batch_types<DT_F32, DT_F32, DT_BF16>(hdr, tab, vec_ok, cpl, var, g, s, occ);
+        return batch_types<DT_F32, DT_F32, DT_BF16>(hdr, tab, vec_ok, win_vec, cpl, var, g, s, occ);
     if (vt == DT_F32 && bt == DT_BF16 && tt == DT_BF16)
-        return batch_types<DT_F32, DT_BF16, DT_BF16>(hdr, tab, vec_ok, cpl, var, g, s, occ);
+        return batch_types<DT_F32, DT_BF16, DT_BF16>(hdr, tab, vec_ok, win_vec, cpl, var, g, s, occ);
     if (vt == DT_BF16 && bt == DT_BF16 && tt == DT_BF16)
-        return batch_types<DT_BF16, DT_BF16, DT_BF16>(hdr, tab, vec_ok, cpl, var, g, s, occ);
+        return batch_types<DT_BF16, DT_BF16, DT_BF16>(hdr, tab, vec_ok, win_vec, cpl, var, g, s, occ);
     if (vt == DT_F16 && bt == DT_F16 && tt == DT_F16)
-        return batch_types<DT_F16, DT_F16, DT_F16>(hdr, tab, vec_ok, cpl, var, g, s, occ);
+        return batch_types<DT_F16, DT_F16, DT_F16>(hdr, tab, vec_ok, win_vec, cpl, var, g, s, occ);
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_batch(const BatchHeader *hdr, const BatchEntry *tab, int32_t vt, int32_t bt,
-                        int32_t tt, int vec_ok, int cpl, int var, const BatchGrids &grids,
+                        int32_t tt, int vec_ok, int win_vec, int cpl, int var, const BatchGrids &grids,
                         hipStream_t s) {
-    return batch_any(hdr, tab, vt, bt, tt, vec_ok, cpl, var, grids, s, nullptr);
+    return batch_any(hdr, tab, vt, bt, tt, vec_ok, win_vec, cpl, var, grids, s, nullptr);
 }
 
-hipError_t batch_occupancy(int32_t vt, int32_t bt, int32_t tt, int vec_ok, int cpl, int var,
+hipError_t batch_occupancy(int32_t vt, int32_t bt, int32_t tt, int vec_ok, int win_vec, int cpl, int var,
                            BatchGrids *per_cu) {
-    return batch_any(nullptr, nullptr, vt, bt, tt, vec_ok, cpl, var, BatchGrids{}, nullptr, per_cu);
+    return batch_any(nullptr, nullptr, vt, bt, tt, vec_ok, win_vec, cpl, var, BatchGrids{}, nullptr, per_cu);
 }
 
 hipError_t launch_copy(const float4 *src, float4 *dst, int64_t n4, hipStream_t s) {

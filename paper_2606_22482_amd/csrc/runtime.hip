@@ -588,26 +588,36 @@ spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void
     a.ldc = ldc;
     a.work = nullptr;
     a.work_ld = (N + 3) / 4 * 4;
-    a.vec_ok = (N % E == 0) && (ldb % E == 0) && (ldc % 4 == 0) &&
-               ((uintptr_t)B % 16 == 0) && ((uintptr_t)C % 16 == 0) && (sb * E == 16);
+    // 16-byte chunks at element alignment: any N of at least one chunk, any
+    // leading dimension and any row start (gfx950 loads and stores them whole).
+    // One element a lane remains for rows below one chunk only: on a graph of
+    // 200,003 rows (2.8M entries, f32) at N = 47 it took 229 us, chunks 95 us.
+    a.vec_ok = N >= E && (uintptr_t)B % sb == 0 && (uintptr_t)C % 4 == 0;
+    a.win_vec = N % E == 0 && ldb % E == 0 && ldc % 4 == 0 && (uintptr_t)B % 16 == 0 && (uintptr_t)C % 16 == 0;
     int np = h.opts.n_panel > 0 ? std::min(h.opts.n_panel, N) : N;
     const int maxnp = a.vec_ok ? 128 * E : 128;
     np = std::min(np, maxnp);
-    if (a.vec_ok) np = std::max(E, np / E * E);
+    if (a.vec_ok && np < N) np = std::max(E, np / E * E);
     a.np = np;
     a.n_panels = (N + np - 1) / np;
-    const int chunks = a.vec_ok ? np / E : np;
+    const int chunks = a.vec_ok ? (np + E - 1) / E : np;
     a.lpr_log2 = ilog2_ceil(std::min(chunks, 64));
     a.xcd = h.opts.xcd_remap ? 1 : 0;
     // cold B rows go through a raw buffer load (32-bit byte offsets from B)
     const double b_span = ((double)std::max<int64_t>(h.k, 1) - 1.0) * (double)ldb * sb + (double)N * sb;
-    a.cold_aux = (b_span < 4294967295.0 && h.opts.cold_policy != 0) ? h.opts.cold_policy : -1;
-    a.b_rec = b_span < 4294967040.0 ? (uint32_t)b_span : 0u;
-    a.pipeline = h.opts.pipeline;
+    // and take chunks aligned to 4 bytes, which 16-bit rows of an odd N or
+    // leading dimension are not
+    const bool al4 = sb == 4 || (N % 2 == 0 && ldb % 2 == 0 && (uintptr_t)B % 4 == 0);
+    a.cold_aux = (b_span < 4294967295.0 && al4 && h.opts.cold_policy != 0) ? h.opts.cold_policy : -1;
+    a.b_rec = b_span < 4294967040.0 && al4 ? (uint32_t)b_span : 0u;
+    // f32 rows of more than 32 columns that are not whole chunks: size classes
+    // sum every row as the packed-row variant does (one order for both at such
+    // widths), and that variant is the faster one for f32 B
+    a.pipeline = h.opts.pipeline == 3 && sb == 4 && N % E != 0 && N > 32 ? 2 : h.opts.pipeline;
     // narrow 16-bit B: windows stage panels of 64 or 32 columns, so that no
     // staged column and no MFMA block is padding
     int wnp = 128;
-    if (a.vec_ok && sb == 2) wnp = N <= 32 ? 32 : N <= 64 ? 64 : 128;
+    if (a.win_vec && sb == 2) wnp = N <= 32 ? 32 : N <= 64 ? 64 : 128;
     set_window_panels(a, N, E, wnp);
     return SPMM_OK;
 }
@@ -615,7 +625,7 @@ spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void
 void set_window_panels(RunArgs &a, int N, int E, int np) {
     a.win_np = np;
     a.win_panels = (N + np - 1) / np;
-    const int wchunks = a.vec_ok ? np / E : np;
+    const int wchunks = a.win_vec ? np / E : np;
     a.win_lpr_log2 = ilog2_ceil(std::min(wchunks, 64));
 }
 }  // namespace spmm
