@@ -14,7 +14,7 @@
  *                 a balanced list of work items (Sec. 7, row-window lists).
  *                 The plan is uploaded to the device once.
  *   spmm_run   -- one asynchronous execution on a HIP stream: MFMA over the
- *                 kept tiles with B staged in LDS, FP32 gather-FMA for the
+ *                 kept tiles, each B row loaded once a window, FP32 gather-FMA for the
  *                 remainder, one write of every C row.
  *
  * Conventions for every entry point:

@@ -21,9 +21,9 @@
 //      (row, column) slot, the first entry in CSR order of a repeated pair
 //      winning (an atomic minimum of entry indices); the others stay in the
 //      row's remainder, in CSR order;
-//   4. bitmaps (one kt-bit word per window row, LSB first) and the packed
-//      values in row-major order over the set bits, f32 values rounded to
-//      bf16 to nearest even.
+//   4. bitmaps (one kt-bit word per window row, LSB first) and the tiles'
+//      values, dense (f32 values rounded to bf16 to nearest even); the host
+//      views pack them in row-major order over the set bits.
 // Only O(m + windows + tiles) arrays come back to the host, which builds the
 // schedule (vector items, segments, window items: build_schedule, as for a
 // host plan); the remainder and the tiles go device to device into the plan.
@@ -375,24 +375,25 @@ __global__ __launch_bounds__(kThreads) void k_tvptr(int64_t T, int32_t H, const 
     tile_val_ptr[t] = (int32_t)(t < T ? vpos[t * H] : nv);
 }
 
-// packed values (row-major over set bits) and their CSR entries
-__global__ __launch_bounds__(kThreads) void k_values(int64_t TH, int32_t val_type, const int32_t *__restrict__ src,
+// The tiles' dense values (zero where no entry is) and the CSR entries of the
+// packed values (row-major over set bits), one thread a slot, so that slots,
+// values and entries are read and written side by side.
+__global__ __launch_bounds__(kThreads) void k_values(int64_t slots, int32_t val_type, const int32_t *__restrict__ src,
                                                      const uint32_t *__restrict__ bitmap,
                                                      const int64_t *__restrict__ vpos, const uint8_t *__restrict__ vals,
-                                                     uint16_t *__restrict__ tile_vals, int32_t *__restrict__ tile_src) {
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= TH) return;
-    int64_t q = vpos[i];
-    const uint32_t w = bitmap[i];
-    for (int j = 0; j < kKt; ++j) {
-        if (!((w >> j) & 1u)) continue;
-        const int32_t p = src[i * kKt + j];
-        uint16_t bits;
-        if (val_type == SPMM_F32) bf16_bits_of(reinterpret_cast<const float *>(vals)[p], &bits);
-        else bits = reinterpret_cast<const uint16_t *>(vals)[p];
-        tile_vals[q] = bits;
-        tile_src[q] = p;
-        ++q;
+                                                     uint16_t *__restrict__ tile_dense, int32_t *__restrict__ tile_src) {
+    for (int64_t x = (int64_t)blockIdx.x * kThreads + threadIdx.x; x < slots; x += (int64_t)gridDim.x * kThreads) {
+        const int64_t i = x / kKt;
+        const int j = (int)(x % kKt);
+        const uint32_t w = bitmap[i];
+        uint16_t bits = 0;
+        if ((w >> j) & 1u) {
+            const int32_t p = src[x];
+            if (val_type == SPMM_F32) bf16_bits_of(reinterpret_cast<const float *>(vals)[p], &bits);
+            else bits = reinterpret_cast<const uint16_t *>(vals)[p];
+            tile_src[vpos[i] + __popc(w & ((1u << j) - 1u))] = p;
+        }
+        tile_dense[x] = bits;
     }
 }
 
@@ -679,13 +680,13 @@ spmm_status plan_device_mixed(const spmm_csr *A, int32_t n, int32_t b_type, int3
         int32_t *rem_col, *rem_aux;
         uint8_t *rem_val;
         uint32_t *tile_bitmap;
-        uint16_t *tile_vals;
+        uint16_t *tile_dense;
         int64_t *vcnt, *vpos;
         int32_t *tile_val_ptr;
         SPMM_ALLOC(rem_col, nrem);
         SPMM_ALLOC(rem_val, nrem * sval);
         SPMM_ALLOC(tile_bitmap, T * H);
-        SPMM_ALLOC(tile_vals, nv);
+        SPMM_ALLOC(tile_dense, T * H * kKt);
         SPMM_ALLOC(vcnt, T * H);
         SPMM_ALLOC(vpos, T * H);
         SPMM_ALLOC(tile_val_ptr, T + 1);
@@ -698,13 +699,14 @@ spmm_status plan_device_mixed(const spmm_csr *A, int32_t n, int32_t b_type, int3
         if (m > 0)
             hipLaunchKernelGGL(k_remainder, dim3(row_blocks(m)), dim3(kThreads), 0, s, m, sval, rp32, A->colidx,
                                static_cast<const uint8_t *>(A->vals), in_tile, rem_ptr, rem_col, rem_val, rem_aux);
-        // 4. bitmaps, value offsets, packed values
+        // 4. bitmaps, value offsets, values
         if (T > 0) {
             hipLaunchKernelGGL(k_bitmap, dim3(blocks_for(T * H)), dim3(kThreads), 0, s, T * H, src, tile_bitmap, vcnt);
             SPMM_TRY_HIP(scan64(vcnt, vpos, T * H, 0, sums, s), "scan");
             hipLaunchKernelGGL(k_tvptr, dim3(blocks_for(T + 1)), dim3(kThreads), 0, s, T, H, vpos, nv, tile_val_ptr);
-            hipLaunchKernelGGL(k_values, dim3(blocks_for(T * H)), dim3(kThreads), 0, s, T * H, A->val_type, src,
-                               tile_bitmap, vpos, static_cast<const uint8_t *>(A->vals), tile_vals, rem_aux + nrem);
+            hipLaunchKernelGGL(k_values, dim3((unsigned)std::min<int64_t>(blocks_for(T * H * kKt), 65536)),
+                               dim3(kThreads), 0, s, T * H * kKt, A->val_type, src, tile_bitmap, vpos,
+                               static_cast<const uint8_t *>(A->vals), tile_dense, rem_aux + nrem);
         }
         if (k > 0)
             hipLaunchKernelGGL(k_mcount_seen, dim3((unsigned)std::min<int64_t>(blocks_for(k), 4096)), dim3(kThreads),
@@ -742,9 +744,8 @@ spmm_status plan_device_mixed(const spmm_csr *A, int32_t n, int32_t b_type, int3
         da.rem_val = rem_val;
         da.tile_cols = tile_cols;
         da.tile_bitmap = tile_bitmap;
-        da.tile_vals = tile_vals;
+        da.tile_dense = tile_dense;
         da.nrem = (size_t)nrem;
-        da.nvals = (size_t)nv;
         const int64_t S = (int64_t)h.seg_row.size();
         if (S > 0) {
             int32_t *sb, *se, *sk;

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 namespace spmm {
 
@@ -28,15 +29,16 @@ struct DevPlan {
     const int32_t *win_seg;    // [n_win]
     const int32_t *win_order;  // [n_win], or null when windows run in id order
     const int32_t *tile_cols;  // [T*kt]
-    const uint32_t *tile_bitmap;  // [T*H]
-    const int32_t *tile_val_ptr;  // [T+1]
-    const uint16_t *tile_vals;
+    const uint16_t *tile_dense;  // [(T+1)*H*kt] bf16 / f16 bits, row-major, zero where no entry is;
+                                 // tile T is all zeros
+    int32_t n_tiles;             // T
+    const uint32_t *tile_bitmap; // [T*H] of a plan partitioned on the device (for its host views), else null
     int32_t n_wpart, win_tmax;  // window partial items; tiles an owner item computes itself
     const int32_t *win_part;    // [n_win+1]
     const int32_t *wpart_win;   // [n_wpart]
     const int32_t *wpart_t0;    // [n_wpart]
     const int32_t *wpart_t1;    // [n_wpart]
-    const uint16_t *zeros;      // 256 zero bytes (source of staged padding columns)
+    const uint16_t *zeros;      // 256 zero bytes (the B row of no column, for plain loads)
     // co-scheduled execution (last-finisher combine)
     const int32_t *seg_row;     // [n_seg] row of each segment
     const int32_t *seg_win;     // [n_seg] window holding the segment's row, -1 for a vector row;
@@ -58,14 +60,13 @@ struct RunArgs {
                         // [n_wpart * H * work_ld]
     int32_t work_ld;    // row stride of `work` (N rounded up to 4)
     int32_t vec_ok;     // rows hold at least one 16-byte chunk of B (4 f32, 8 16-bit elements)
-    int32_t win_vec;    // windows: rows of B and C are whole, aligned 16-byte chunks
     int32_t np;         // columns per panel of the vector / segment kernels
     int32_t n_panels;
     int32_t lpr_log2;   // log2(lanes per entry group) for the vector / segment kernels
     int32_t xcd;        // remap consecutive items onto one XCD
     int32_t win_panels; // panels of the window items (win_np columns each)
-    int32_t win_np;     // columns per window panel: 128, or 64 / 32 for 16-bit B with N <= 64
-    int32_t win_lpr_log2;
+    int32_t win_np;     // columns per window panel: 16, 32, 64 or (16-bit B) 128
+    int32_t win_subs;   // waves of a window item, each with an equal share of its 16-row blocks
     int32_t cold_aux;   // buffer-load policy bits for non-hot B rows; -1: plain loads for all
     uint32_t b_rec;     // bytes of B reachable through a buffer resource (its span); 0 when B
                         // spans 4 GiB or more or its chunks are not aligned to 4 bytes (plain loads)
@@ -73,7 +74,8 @@ struct RunArgs {
                         // 3 rows packed by size class
     // co-scheduled execution
     int32_t *cnt;       // arrival counters: [n_panels * n_seg] per split vector row (at its first
-                        // segment id), then [win_panels * n_dep] per window slot; zero between runs
+                        // segment id), then [win_panels * n_dep * win_subs] per share of a
+                        // window slot; zero between runs
     float *dep;         // window slots: [n_dep][2][H][work_ld] (MFMA result, rows' remainders)
     uint32_t ws_rec;    // bytes of the workspace (below 4 GiB for a co-scheduled run)
     int32_t seg_blocks; // workgroups of segment waves in a fused launch (a multiple of 8)
@@ -83,12 +85,12 @@ struct RunArgs {
 };
 
 // One matrix of a batched execution.  `*_end` are exclusive prefix sums of
-// the global item counts (segment waves, vector waves, window workgroups), so
+// the global item counts (segment, vector and window waves), so
 // a persistent kernel can walk the table forward as its item ids increase.
 struct BatchEntry {
     DevPlan P;
     RunArgs a;
-    int32_t seg_end, vec_end, win_end, wpart_end;      // exclusive prefix over the table
+    int32_t seg_end, vec_end, win_end, wpart_end;      // exclusive prefix over the table (all in waves)
     int32_t seg_base, vec_base, win_base, wpart_base;  // matrix item index of the first item
 };
 
@@ -109,21 +111,20 @@ struct BatchGrids {
 };
 // Persistent batched launches over a device table (header + entries).
 hipError_t launch_batch(const BatchHeader *hdr, const BatchEntry *tab, int32_t val_t, int32_t b_t,
-                        int32_t tile_t, int vec_ok, int win_vec, int cpl, int var,
-                        const BatchGrids &grids, hipStream_t s);
+                        int32_t tile_t, int vec_ok, int cpl, int var, const BatchGrids &grids,
+                        hipStream_t s);
 // Resident workgroups per CU of each batched kernel of this variant.
-hipError_t batch_occupancy(int32_t val_t, int32_t b_t, int32_t tile_t, int vec_ok, int win_vec,
-                           int cpl, int var, BatchGrids *per_cu);
+hipError_t batch_occupancy(int32_t val_t, int32_t b_t, int32_t tile_t, int vec_ok, int cpl,
+                           int var, BatchGrids *per_cu);
 
 // dtype codes as in spmm.h
 hipError_t launch_segment(const DevPlan &P, int32_t val_t, int32_t b_t, const RunArgs &a,
                           hipStream_t s);
 hipError_t launch_vector(const DevPlan &P, int32_t val_t, int32_t b_t, const RunArgs &a,
                          hipStream_t s);
+// window owners, or (partial) the windows' partial items
 hipError_t launch_window(const DevPlan &P, int32_t val_t, int32_t b_t, int32_t tile_t,
-                         const RunArgs &a, hipStream_t s);
-hipError_t launch_window_partial(const DevPlan &P, int32_t val_t, int32_t b_t, int32_t tile_t,
-                                 const RunArgs &a, hipStream_t s);
+                         const RunArgs &a, hipStream_t s, bool partial);
 hipError_t launch_copy(const float4 *src, float4 *dst, int64_t n4, hipStream_t s);
 
 // co-scheduled execution (fused.hip): the vector path (segments + vector
@@ -158,6 +159,42 @@ hipError_t launch_one_grid(const DevPlan &P, int32_t val_t, int32_t b_t, int32_t
                            const RunArgs &a, hipStream_t s);
 // p[0 .. n) = 0 by a kernel (capturable, unlike a memset node)
 hipError_t launch_zero(int32_t *p, int64_t n, hipStream_t s);
+
+// Calls f(MB, MBW, CW, BUF) (integral constants; see window_item) for the
+// windows of a run: blocks of a window (0: taken from the plan), blocks a wave
+// takes, columns a lane takes, B through a buffer resource.
+template <int BT, typename F>
+inline hipError_t window_shape(const DevPlan &P, const RunArgs &a, F &&f) {
+    using std::integral_constant;
+    auto columns = [&](auto mb, auto mbw, auto buf) -> hipError_t {
+        if constexpr (BT != 0)
+            if (a.win_np == 128) return f(mb, mbw, integral_constant<int, 8>{}, buf);
+        if (a.win_np == 64) return f(mb, mbw, integral_constant<int, 4>{}, buf);
+        if (a.win_np == 32) return f(mb, mbw, integral_constant<int, 2>{}, buf);
+        if constexpr (decltype(mbw)::value == 1)
+            if (a.win_np == 16) return f(mb, mbw, integral_constant<int, 1>{}, buf);
+        return hipErrorInvalidValue;
+    };
+    const integral_constant<int, 0> any;
+    const integral_constant<int, 1> one;
+    const integral_constant<int, 2> two;
+    const integral_constant<int, 4> four;
+    const integral_constant<bool, true> buf;
+    const integral_constant<bool, false> plain;
+    if (P.H == 16 * a.win_subs) {
+        if (!a.b_rec) return columns(any, one, plain);
+        return P.H == 16 ? columns(one, one, buf) : columns(any, one, buf);
+    }
+    if (P.H == 64 && a.win_subs == 2) {
+        if (a.b_rec) return columns(four, two, buf);
+        if constexpr (BT != 0) return columns(four, two, plain);
+    }
+    if (P.H == 64 && a.win_subs == 1) {
+        if (a.b_rec) return columns(four, four, buf);
+        if constexpr (BT != 0) return columns(four, four, plain);
+    }
+    return hipErrorInvalidValue;
+}
 
 // chunk width (elements per 16-byte load) of a B type
 inline int chunk_elems(int32_t b_t) { return b_t == 0 ? 4 : 8; }

@@ -10,11 +10,11 @@
 //       caller's stream (fork and join by events), that run concurrently:
 //       the vector path (segment waves, then vector-item waves) and the MFMA
 //       path (window partial items, then window owners).  Each grid keeps its
-//       own register and LDS allocation, so the vector path keeps its
-//       occupancy next to the LDS-heavy windows.
+//       own register allocation, so the vector path keeps its occupancy next
+//       to the windows.
 //   one grid -- all four item kinds in one launch (workgroup ranges of window
 //       partials, window owners, segments, vector items); every workgroup is
-//       given the window item's LDS and registers.
+//       given the window item's registers.
 //
 // Results that need several items are finished by their last contributor
 // (items.hpp, co-scheduled execution), so neither form has a barrier or a
@@ -45,19 +45,16 @@ __device__ __forceinline__ void vector_path(const DevPlan &P, const RunArgs &a, 
 
 // Workgroup b of the MFMA path: window partial items first, then the owners
 // (in window launch order, each XCD taking consecutive windows).
-template <int VT, int BT, int TT, int MB, int E, int CPL, int NPW = 128>
-__device__ __forceinline__ void mfma_path(const DevPlan &P, const RunArgs &a, int b, WinSmem<MB, NPW> &sm) {
-    if (b < a.wpart_blocks) {
-        if (b < P.n_wpart * a.win_panels)
-            window_item<VT, BT, TT, MB, E, CPL, MB, true, NPW>(P, a, b, sm, true);
-    } else {
-        // padding workgroups of the one-grid form (j beyond the range) stay
-        // idle: the remap is a permutation of [0, win_blocks) only
-        const int j = b - a.wpart_blocks;
-        if (j >= a.win_blocks) return;
-        const int item = a.xcd ? remap_block(j, a.win_blocks) : j;
-        window_item<VT, BT, TT, MB, E, CPL, MB, true, NPW>(P, a, item, sm, false);
-    }
+template <int VT, int BT, int TT, int MB, int MBW, int CW, bool BUF>
+__device__ __forceinline__ void mfma_path(const DevPlan &P, const RunArgs &a, int b) {
+    const bool partial = b < a.wpart_blocks;
+    // padding workgroups of the one-grid form (j beyond the range) stay idle:
+    // the remap is a permutation of [0, win_blocks) only
+    const int j = partial ? b : b - a.wpart_blocks;
+    if (!partial && j >= a.win_blocks) return;
+    const int wid = (!partial && a.xcd ? remap_block(j, a.win_blocks) : j) * 4 + wave_id();
+    if (wid < (partial ? P.n_wpart : P.n_win) * a.win_panels * a.win_subs)
+        window_item<VT, BT, TT, MB, MBW, CW, BUF, true>(P, a, wid, partial);
 }
 
 template <int VT, int BT, int E, int CPL, int VAR>
@@ -65,19 +62,17 @@ __global__ __launch_bounds__(256) void vector_path_kernel(DevPlan P, RunArgs a) 
     vector_path<VT, BT, E, CPL, VAR>(P, a, blockIdx.x);
 }
 
-template <int VT, int BT, int TT, int MB, int E, int CPL, int NPW>
-__global__ __launch_bounds__(256) void mfma_path_kernel(DevPlan P, RunArgs a) {
-    __shared__ WinSmem<MB, NPW> sm;
-    mfma_path<VT, BT, TT, MB, E, CPL, NPW>(P, a, blockIdx.x, sm);
+template <int VT, int BT, int TT, int MB, int MBW, int CW, bool BUF>
+__global__ __launch_bounds__(256, (window_waves<MBW, CW>())) void mfma_path_kernel(DevPlan P, RunArgs a) {
+    mfma_path<VT, BT, TT, MB, MBW, CW, BUF>(P, a, blockIdx.x);
 }
 
 // The MFMA path's workgroups (padded to a multiple of 8), then the vector path's.
-template <int VT, int BT, int TT, int MB, int E, int CPL, int VAR>
-__global__ __launch_bounds__(256) void one_grid_kernel(DevPlan P, RunArgs a) {
-    __shared__ WinSmem<MB> sm;
+template <int VT, int BT, int TT, int E, int CPL, int VAR>
+__global__ __launch_bounds__(256, 2) void one_grid_kernel(DevPlan P, RunArgs a) {
     const int wb = a.wpart_blocks + ((a.win_blocks + 7) & ~7);
     const int b = blockIdx.x;
-    if (b < wb) mfma_path<VT, BT, TT, MB, E, CPL>(P, a, b, sm);
+    if (b < wb) mfma_path<VT, BT, TT, 0, 1, E, true>(P, a, b);
     else vector_path<VT, BT, E, CPL, VAR>(P, a, b - wb);
 }
 
@@ -113,34 +108,15 @@ hipError_t launch_vector_path(const DevPlan &P, int32_t vt, int32_t bt, const Ru
     return hipErrorInvalidValue;
 }
 
-template <int VT, int BT, int TT, int MB>
-static hipError_t mp_mb(const DevPlan &P, const RunArgs &a, hipStream_t s) {
-    constexpr int EV = BT == DT_F32 ? 4 : 8;
-    const dim3 grid((unsigned)(a.wpart_blocks + a.win_blocks)), block(256);
-    if (!a.win_vec) {
-        launch_kernel((mfma_path_kernel<VT, BT, TT, MB, 1, 2, 128>), grid, block, 0, s, P, a);
-    } else if constexpr (BT == DT_F32) {
-        launch_kernel((mfma_path_kernel<VT, BT, TT, MB, EV, 1, 128>), grid, block, 0, s, P, a);
-    } else {
-        // narrow 16-bit B stages 64- or 32-column panels
-        if (a.win_np == 128)
-            launch_kernel((mfma_path_kernel<VT, BT, TT, MB, EV, 1, 128>), grid, block, 0, s, P, a);
-        else if (a.win_np == 64)
-            launch_kernel((mfma_path_kernel<VT, BT, TT, MB, EV, 1, 64>), grid, block, 0, s, P, a);
-        else
-            launch_kernel((mfma_path_kernel<VT, BT, TT, MB, EV, 1, 32>), grid, block, 0, s, P, a);
-    }
-    return hipGetLastError();
-}
-
 template <int VT, int BT, int TT>
 static hipError_t mp_types(const DevPlan &P, const RunArgs &a, hipStream_t s) {
-    switch (P.H) {
-    case 16: return mp_mb<VT, BT, TT, 1>(P, a, s);
-    case 32: return mp_mb<VT, BT, TT, 2>(P, a, s);
-    case 64: return mp_mb<VT, BT, TT, 4>(P, a, s);
-    default: return hipErrorInvalidValue;
-    }
+    const dim3 grid((unsigned)(a.wpart_blocks + a.win_blocks)), block(256);
+    return window_shape<BT>(P, a, [&](auto mb, auto mbw, auto cw, auto buf) {
+        launch_kernel((mfma_path_kernel<VT, BT, TT, decltype(mb)::value, decltype(mbw)::value, decltype(cw)::value,
+                                        decltype(buf)::value>),
+                      grid, block, 0, s, P, a);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_mfma_path(const DevPlan &P, int32_t vt, int32_t bt, int32_t tt, const RunArgs &a,
@@ -154,34 +130,25 @@ hipError_t launch_mfma_path(const DevPlan &P, int32_t vt, int32_t bt, int32_t tt
 }
 
 // One grid: built for 16-byte chunks with one chunk per lane, the packed
-// vector variants (2, 3), which cover the defaults, and 128-column window
-// panels; other plans report hipErrorNotSupported and run as two grids.
-template <int VT, int BT, int TT, int MB>
-static hipError_t og_mb(const DevPlan &P, const RunArgs &a, hipStream_t s) {
+// vector variants (2, 3), which cover the defaults, and window panels of one
+// such chunk a lane; other plans report hipErrorNotSupported and run as two
+// grids.
+template <int VT, int BT, int TT>
+static hipError_t og_types(const DevPlan &P, const RunArgs &a, hipStream_t s) {
     constexpr int EV = BT == DT_F32 ? 4 : 8;
     const unsigned wb = (unsigned)(a.wpart_blocks + ((a.win_blocks + 7) & ~7));
     const dim3 grid(wb + (unsigned)(a.seg_blocks + a.vec_blocks)), block(256);
     if (a.pipeline == 3)
-        launch_kernel((one_grid_kernel<VT, BT, TT, MB, EV, 1, 3>), grid, block, 0, s, P, a);
+        launch_kernel((one_grid_kernel<VT, BT, TT, EV, 1, 3>), grid, block, 0, s, P, a);
     else
-        launch_kernel((one_grid_kernel<VT, BT, TT, MB, EV, 1, 2>), grid, block, 0, s, P, a);
+        launch_kernel((one_grid_kernel<VT, BT, TT, EV, 1, 2>), grid, block, 0, s, P, a);
     return hipGetLastError();
-}
-
-template <int VT, int BT, int TT>
-static hipError_t og_types(const DevPlan &P, const RunArgs &a, hipStream_t s) {
-    switch (P.H) {
-    case 16: return og_mb<VT, BT, TT, 1>(P, a, s);
-    case 32: return og_mb<VT, BT, TT, 2>(P, a, s);
-    case 64: return og_mb<VT, BT, TT, 4>(P, a, s);
-    default: return hipErrorInvalidValue;
-    }
 }
 
 bool one_grid_supported(int32_t b_t, const RunArgs &a) {
     const int ev = b_t == DT_F32 ? 4 : 8;
-    return a.win_vec && (a.np + ev - 1) / ev <= 64 && (a.pipeline == 2 || a.pipeline == 3) &&
-           a.win_np == 128;
+    return a.vec_ok && (a.np + ev - 1) / ev <= 64 && (a.pipeline == 2 || a.pipeline == 3) &&
+           a.win_np == 16 * ev && a.b_rec != 0;
 }
 
 hipError_t launch_one_grid(const DevPlan &P, int32_t vt, int32_t bt, int32_t tt, const RunArgs &a,

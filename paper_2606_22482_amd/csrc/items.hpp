@@ -10,14 +10,12 @@
 //               gather-FMA over each row's remainder (Sec. 5.1, gather then
 //               accumulate), or the fixed-order sum of its segment partials,
 //               then one write of the C row.
-//   window   -- one workgroup per (row window, column panel of 128, or of 64
-//               or 32 for narrow 16-bit B): the B rows
-//               of the window's compacted tile columns are staged in LDS once
-//               and reused by every row of the window (Sec. 6.2, intra-core
-//               reuse; Sec. 5.1, matrix-engine execution), each tile's bitmap
-//               and packed values are expanded into dense rows in LDS and read
-//               as MFMA operands (bf16 / f16 in, f32 accumulate), then each
-//               row adds its remainder and is written once.
+//   window   -- one wavefront per (row window or a share of its rows, column
+//               panel of 128, 64, 32 or 16): the B rows of each tile's
+//               compacted columns are loaded straight into MFMA operand order
+//               (Sec. 5.1, matrix-engine execution), each tile's dense values
+//               are the other operand (bf16 / f16 in, f32 accumulate), then
+//               each row adds its remainder and is written once.
 //
 // Summation order of a remainder segment (identical in every kernel that
 // computes one, so a row's bits depend only on the plan and N, never on the
@@ -37,7 +35,6 @@ enum { DT_F32 = 0, DT_BF16 = 1, DT_F16 = 2 };
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // 16 bytes at element alignment: a row of N columns with any leading dimension
 // starts anywhere, and gfx950 reads and writes 16 bytes at such an address in
@@ -65,13 +62,6 @@ __device__ __forceinline__ int panel_col(int p, int np, int n) {
 __device__ __forceinline__ float bf16_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
 __device__ __forceinline__ float f16_to_f32(uint32_t h) {
     return (float)__builtin_bit_cast(_Float16, (unsigned short)h);
-}
-
-// float -> bf16 bits, round to nearest even; NaN stays a quiet NaN.
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x007FFFFFu)) return (u >> 16) | 0x40u;
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
 template <int DT>
@@ -437,20 +427,6 @@ __device__ __forceinline__ void gather_fma(const int (&col)[U], const float (&v)
     }
 }
 
-// acc += v_u * b_u over the entries below p1, in entry order (the FMA half of
-// gather_fma, for B chunks gathered earlier by the caller).
-template <int BT, int E, int CPL, int U>
-__device__ __forceinline__ void fma_rows(const float (&v)[U], const Raw<BT, E> (&b)[U][CPL], int p,
-                                         int p1, const Lanes &L, float (&acc)[CPL][E]) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        if (p + u * L.groups < p1) {
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) fma_raw<BT, E>(v[u], b[u][c], acc[c]);
-        }
-    }
-}
-
 template <int E, int CPL>
 __device__ __forceinline__ void chunk_layout(int ncol0, int ncols, const Lanes &L, bool (&cok)[CPL],
                                              int64_t (&coff)[CPL]) {
@@ -642,42 +618,32 @@ __device__ __forceinline__ bool wave_arrive(int32_t *cnt, int target) {
     return old == target - 1;
 }
 
-// A whole workgroup arrives (after all its threads' stores); `flag` is LDS.
-__device__ __forceinline__ bool group_arrive(int32_t *cnt, int target, int32_t *flag) {
-    stores_done();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const int old = atomicAdd(cnt, 1);
-        const bool last = old == target - 1;
-        if (last) atomicExch(cnt, 0);
-        *flag = last ? 1 : 0;
-    }
-    __syncthreads();
-    return *flag != 0;
+// Counter of window slot `dep` in window panel q (win_np columns) and row
+// share `sub` (one of the win_subs waves of a window item).
+__device__ __forceinline__ int32_t *win_counter(const DevPlan &P, const RunArgs &a, int q, int dep, int sub) {
+    return a.cnt + (int64_t)a.n_panels * P.n_seg + ((int64_t)q * P.n_dep + dep) * a.win_subs + sub;
 }
 
-// Counter of window slot `dep` in window panel q (win_np columns).
-__device__ __forceinline__ int32_t *win_counter(const DevPlan &P, const RunArgs &a, int q, int dep) {
-    return a.cnt + (int64_t)a.n_panels * P.n_seg + (int64_t)q * P.n_dep + dep;
-}
-
-// Arrivals a window panel waits for: its owner, its partial items, and every
-// segment panel (width np) overlapping the window panel for each segment of
-// the window's split rows.
+// Arrivals each row share of a window panel waits for: its owner, its partial
+// items, and every segment panel (width np) overlapping the window panel for
+// each segment of the window's split rows (a segment arrives at every share).
 __device__ __forceinline__ int win_target(const DevPlan &P, const RunArgs &a, int w, int q) {
     const int c0 = q * a.win_np, c1 = min(P.n, c0 + a.win_np) - 1;
     return 1 + (P.win_part[w + 1] - P.win_part[w]) + P.win_nsseg[w] * (c1 / a.np - c0 / a.np + 1);
 }
 
-// The last arrival of window w, panel q: for each window row, its MFMA result
-// plus the partial tiles' results in tile order, plus its remainder (the
-// owner's sum, or the row's segment partials in segment order), written to C.
-// Thread t of T participating threads takes 4-column chunks t, t + T, ... of
-// the window's rows x panel columns (the workspace rows are padded to a
-// multiple of 4 columns, so a chunk load stays in its row).
+// The last arrival of window w, panel q, row share `sub`: for each of its
+// rows, the MFMA result plus the partial tiles' results in tile order, plus
+// the remainder (the owner's sum, or the row's segment partials in segment
+// order), written to C.  Lane t takes 4-column chunks t, t + 64, ... of the
+// rows x panel columns (the workspace rows are padded to a multiple of 4
+// columns, so a chunk load stays in its row).
+// UN: chunks whose loads a lane has in flight together (the parts come past
+// L2, some microseconds each way).
+template <int UN>
 __device__ __forceinline__ void window_combine(const DevPlan &P, const RunArgs &a, int w, int q, int dep,
-                                               int t, int T) {
-    const int H = P.H;
+                                               int sub) {
+    const int H = P.H, rows = H / a.win_subs;
     const int ncol0 = q * a.win_np, ncols = min(a.win_np, P.n - ncol0), nch = (ncols + 3) >> 2;
     const int pa = P.win_part[w], pb = P.win_part[w + 1];
     const int64_t ld = a.work_ld;
@@ -685,42 +651,60 @@ __device__ __forceinline__ void window_combine(const DevPlan &P, const RunArgs &
     const int64_t wp0 = (int64_t)P.n_seg * ld;                                // window partials
     const int64_t cs0 = wp0 + ((int64_t)H * P.n_wpart + (int64_t)dep * 2 * H) * ld;  // slot: MFMA result
     const int64_t rm0 = cs0 + (int64_t)H * ld;                                // slot: remainders
-    for (int u = t; u < H * nch; u += T) {
-        const int s = u / nch, c = u - s * nch;
-        const int r = P.windows[(int64_t)w * H + s];
-        if (r < 0) continue;
-        const int64_t col = ncol0 + 4 * c;
-        f32x4 v = ld_dev4(rs, cs0 + (int64_t)s * ld + col);
+    const int total = rows * nch;
+    for (int u0 = threadIdx.x & 63; u0 < total; u0 += 64 * UN) {
+        int r[UN], sid[UN], s[UN], c[UN];
+#pragma unroll
+        for (int i = 0; i < UN; ++i) {
+            const int u = min(u0 + 64 * i, total - 1);
+            s[i] = sub * rows + u / nch;
+            c[i] = u % nch;
+            r[i] = P.windows[(int64_t)w * H + s[i]];
+            sid[i] = P.win_row_sid[(int64_t)w * H + s[i]];
+        }
+        f32x4 v[UN], y[UN];
+#pragma unroll
+        for (int i = 0; i < UN; ++i) {
+            const int64_t col = ncol0 + 4 * c[i];
+            v[i] = ld_dev4(rs, cs0 + (int64_t)s[i] * ld + col);
+            // (of a split row: its first segment's partial)
+            y[i] = ld_dev4(rs, (sid[i] >= 0 ? (int64_t)sid[i] * ld : rm0 + (int64_t)s[i] * ld) + col);
+        }
         for (int k0 = pa; k0 < pb; k0 += 4) {
-            f32x4 x[4];
+            f32x4 x[UN][4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) x[i] = ld_dev4(rs, wp0 + ((int64_t)min(k0 + i, pb - 1) * H + s) * ld + col);
+            for (int i = 0; i < UN; ++i)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (k0 + i < pb) v += x[i];
+                for (int k = 0; k < 4; ++k)
+                    x[i][k] = ld_dev4(rs, wp0 + ((int64_t)min(k0 + k, pb - 1) * H + s[i]) * ld + ncol0 + 4 * c[i]);
+#pragma unroll
+            for (int i = 0; i < UN; ++i)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (k0 + k < pb) v[i] += x[i][k];
         }
-        f32x4 y;
-        const int sid0 = P.win_row_sid[(int64_t)w * H + s];
-        if (sid0 >= 0) {
-            const int len = P.rem_ptr[r + 1] - P.rem_ptr[r];
-            const int ns = (len + P.seg_len - 1) / P.seg_len;
-            y = ld_dev4(rs, (int64_t)sid0 * ld + col);
-            for (int j0 = 1; j0 < ns; j0 += 4) {
-                f32x4 x[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) x[i] = ld_dev4(rs, (int64_t)(sid0 + min(j0 + i, ns - 1)) * ld + col);
+        for (int i = 0; i < UN; ++i) {
+            if (u0 + 64 * i >= total || r[i] < 0) continue;
+            const int64_t col = ncol0 + 4 * c[i];
+            if (sid[i] >= 0) {
+                const int len = P.rem_ptr[r[i] + 1] - P.rem_ptr[r[i]];
+                const int ns = (len + P.seg_len - 1) / P.seg_len;
+                for (int j0 = 1; j0 < ns; j0 += 4) {
+                    f32x4 x[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (j0 + i < ns) y += x[i];
+                    for (int k = 0; k < 4; ++k) x[k] = ld_dev4(rs, (int64_t)(sid[i] + min(j0 + k, ns - 1)) * ld + col);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (j0 + k < ns) y[i] += x[k];
+                }
             }
-        } else {
-            y = ld_dev4(rs, rm0 + (int64_t)s * ld + col);
-        }
-        const f32x4 z = v + y;
-        float *dst = a.C + (int64_t)r * a.ldc + col;
+            const f32x4 z = v[i] + y[i];
+            float *dst = a.C + (int64_t)r[i] * a.ldc + col;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (4 * c + e < ncols) dst[e] = z[e];
+            for (int e = 0; e < 4; ++e)
+                if (4 * c[i] + e < ncols) dst[e] = z[e];
+        }
     }
 }
 
@@ -781,8 +765,9 @@ __device__ __forceinline__ void segment_item(const DevPlan &P, const RunArgs &a,
             const int dep = P.win_dep[w];
             // (the panel's own columns, without those it was widened by: win_target)
             for (int q = panel * a.np / a.win_np; q <= (ncol0 + ncols - 1) / a.win_np; ++q)
-                if (wave_arrive(win_counter(P, a, q, dep), win_target(P, a, w, q)))
-                    window_combine(P, a, w, q, dep, threadIdx.x & 63, 64);
+                for (int sub = 0; sub < a.win_subs; ++sub)
+                    if (wave_arrive(win_counter(P, a, q, dep, sub), win_target(P, a, w, q)))
+                        window_combine<1>(P, a, w, q, dep, sub);
         }
     }
 }
@@ -1152,32 +1137,8 @@ __device__ __forceinline__ void vector_item_var(const DevPlan &P, const RunArgs 
     else vector_item<VT, BT, E, CPL, FUSED>(P, a, wid);
 }
 
-// LDS of a window item: the staged B rows (reused for the f32 C tile), the
-// round's tiles expanded from bitmap + packed values to dense 16-bit rows, and
-// the window's rows, remainder ranges and segment ids.  MB = H / 16; NPWv =
-// the panel width of an item (128 columns, or 64 / 32 for narrow 16-bit B).
-// Staged B row k occupies NPWv * 2 bytes (NCH chunks of 8 elements) with
-// chunk c stored in slot c ^ bswz<NCH>(k): the 8-row groups that one MFMA
-// operand read touches then fall in different banks without padding, so a
-// wave's 64 x 16-byte chunks are one contiguous kilobyte and can be written
-// by one direct global-to-LDS load.
-template <int MB, int NPWv = 128>
-struct WinSmem {
-    static constexpr int NPW = NPWv;         // panel columns of a window item
-    static constexpr int NCH = NPW / 8;      // 16-byte chunks of a staged B row
-    static constexpr int TC = 4;             // tiles staged per round
-    static constexpr int KROWS = TC * 32;    // B rows staged per round
-    static constexpr int BSTR = NPW;         // LDS row stride (16-bit elements)
-    static constexpr int H = MB * 16;
-    static_assert(NPW == 32 || NPW == 64 || NPW == 128, "panel width");
-    __attribute__((aligned(16))) unsigned short Bs[KROWS * BSTR];
-    __attribute__((aligned(16))) unsigned short As[TC * H * 32];  // expanded tiles, row-major
-    int32_t rows[H], rb[H], re[H], sid[H];
-    int32_t flag;  // last-arrival flag of a fused window item
-};
-
 template <int TT>
-__device__ __forceinline__ f32x4 mfma_16x16x32(const u16x8 &a, const u16x8 &b, const f32x4 &c) {
+__device__ __forceinline__ f32x4 mfma_16x16x32(const u32x4 &a, const u32x4 &b, const f32x4 &c) {
     if constexpr (TT == DT_BF16)
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                        __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
@@ -1186,469 +1147,426 @@ __device__ __forceinline__ f32x4 mfma_16x16x32(const u16x8 &a, const u16x8 &b, c
                                                       __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
 
-// 8 consecutive B elements (columns n .. n+7 of B row `col`) as TT bit patterns.
-template <int BT, int TT>
-__device__ __forceinline__ void stage_b8(const void *B, int64_t off, int valid, int vec,
-                                         uint32_t (&w)[4]) {
-    uint32_t h[8];
-    if constexpr (BT == DT_F32) {
-        float f[8];
-        if (vec && valid == 8) {
-            f32x4 x0 = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(B) + off);
-            f32x4 x1 = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(B) + off + 4);
-            f[0] = x0[0]; f[1] = x0[1]; f[2] = x0[2]; f[3] = x0[3];
-            f[4] = x1[0]; f[5] = x1[1]; f[6] = x1[2]; f[7] = x1[3];
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) f[i] = i < valid ? static_cast<const float *>(B)[off + i] : 0.0f;
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) h[i] = f32_to_bf16_bits(f[i]);
-    } else {
-        const unsigned short *p = static_cast<const unsigned short *>(B) + off;
-        if (vec && valid == 8) {
-            u32x4 x = *reinterpret_cast<const u32x4 *>(p);
-            w[0] = x[0]; w[1] = x[1]; w[2] = x[2]; w[3] = x[3];
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) h[i] = i < valid ? p[i] : 0u;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = h[2 * i] | (h[2 * i + 1] << 16);
+// Two f32 as bf16 (round to nearest even), the first in the low half.
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
-typedef short v4i16 __attribute__((ext_vector_type(4)));
+// CW consecutive elements of a B row, as stored (DW dwords; a lone one in a
+// pair, so that the type is a vector in every case).
+template <int BT, int CW>
+struct Chunk {
+    static constexpr int BYTES = CW * (BT == DT_F32 ? 4 : 2), DW = (BYTES + 3) / 4;
+    typedef uint32_t V __attribute__((ext_vector_type(DW < 2 ? 2 : DW)));
+    V w;
+    // at element alignment
+    __device__ __forceinline__ void load(const void *p) {
+        typedef V Ve __attribute__((aligned(2)));
+        typedef uint32_t u32e __attribute__((aligned(2)));
+        if constexpr (BYTES == 2) w[0] = *static_cast<const unsigned short *>(p);
+        else if constexpr (BYTES == 4) w[0] = *static_cast<const u32e *>(p);
+        else w = *static_cast<const Ve *>(p);
+    }
+    // through a buffer resource (an offset at its size or beyond gives zeros)
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+        if constexpr (BYTES == 2) w[0] = buf2<0>(rs, off);
+        else if constexpr (BYTES == 4) w[0] = buf4<0>(rs, off);
+        else if constexpr (BYTES == 8) w = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
+        else w = buf16<0>(rs, off);
+    }
+    __device__ __forceinline__ float f32(int i) const {
+        if constexpr (BT == DT_F32) return __uint_as_float(w[i]);
+        else if constexpr (BT == DT_BF16)
+            return __uint_as_float(i & 1 ? w[i >> 1] & 0xFFFF0000u : w[i >> 1] << 16);
+        else return f16_to_f32(i & 1 ? w[i >> 1] >> 16 : w[i >> 1] & 0xFFFFu);
+    }
+};
 
-// Slot of a chunk in a staged B row (see WinSmem).
-template <int NCH>
-__device__ __forceinline__ int bswz(int k) { return ((k >> 3) & (NCH / 4 - 1)) << 1; }
+// x of lane I of each 16-lane row (DPP row_newbcast), on all its lanes.
+template <int I>
+__device__ __forceinline__ int row16_broadcast(int x) {
+    return __builtin_amdgcn_update_dpp(0, x, 0x150 + I, 0xf, 0xf, true);
+}
 
-// One (window, NPWv-column panel) per workgroup: item in [0, n_win * win_panels),
-// panel innermost, so a window's panels run side by side on one XCD and share
-// its tile data in that XCD's L2.
-// Every thread of the workgroup calls it with the same item.  Per round of up
-// to TC tiles, with one barrier: each thread loads the columns of its own B
-// staging chunks and then those B rows (16-bit B straight into LDS, f32 B
-// through registers, converted to bf16), wave w expands tile w of the round
-// from bitmap + packed values into dense 16-bit rows in LDS, and (first
-// round) the window's row metadata goes to LDS; then MFMA from LDS only (an
-// A operand is one 16-byte read, a B operand two transposing reads).  Then
-// each row adds its remainder and is written once.
-// A workgroup spends most of its life waiting on chains of dependent loads,
-// so the loads of a round are issued level by level (item -> tile range and
-// window rows -> tile columns, bitmaps, value base and row ranges -> B rows,
-// values and remainder entries -> their B rows) with no branch around a load
-// that would make the next one wait; the window order is skipped when it is
-// the identity; the first remainder pass (window rows 0 .. 4G-1, one per lane
-// group) gathers its rows' first U1 entries alongside the first round's tile
-// loads and consumes them after the MFMA rounds.
+// One wavefront's share of a window item: (window, panel of 16 CW columns) and
+// MBW 16-row blocks of the window, MB in all (MB = 0: the plan's, MBW = 1);
+// wid = item * (MB / MBW) + share, panel innermost, so a window's waves run
+// side by side and share its tiles and B rows in L1 and L2.
+//
+// A wave needs no LDS and no barrier: lane (g, c) = (lane / 16, lane % 16)
+// loads CW consecutive elements of the B rows 8g .. 8g+7 of a tile, which is
+// 16 CW columns of 32 rows for the wave.  MFMA operand i takes element i of
+// each lane's chunk, i.e. the 16 columns {c CW + i}: the lane holds rows
+// 8g .. 8g+7 of column c CW + i, as the operand wants it, after one v_perm per
+// pair of rows (16-bit B) or one conversion of the pair (f32 B to bf16).  Its
+// results are rows 4g .. 4g+3 of CW consecutive columns: C is written from
+// the accumulators, and the lane group's rows are those whose remainder
+// entries it gathers, in the same chunks.  The A operand (lane (g, c): row c,
+// columns 8g .. 8g+7) is one aligned 16-byte load: the plan holds its tiles
+// dense on the device (packed values behind a bitmap cost a misaligned load,
+// 64 and more cache accesses where this one takes 16, and 64 instructions to
+// spread them, per row block and tile).
+//
+// NBUF tiles' B rows and values are in flight while one is multiplied, and
+// the tile columns NBUF tiles beyond those.  Loads sit behind no branch inside
+// the loop (a branch makes the compiler wait for all of them): past the last
+// tile they are of no column, which moves no data, and of a tile of zeros
+// behind the plan's own.  A chunk at the end of a ragged panel starts at its last CW columns,
+// and computes the columns it shares with its neighbour twice, from the same
+// operands in the same order.
+//
 // FUSED: partial items and owners of windows with a slot (win_dep) store
-// their parts in the workspace and arrive at the window panel's counter; the
-// last arrival combines (window_combine).  Owners skip split rows, which the
-// combine takes from the segments' partials.
-template <int VT, int BT, int TT, int MB, int E, int CPL, int SMB, bool FUSED = false, int NPWv = 128>
-__device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, int item,
-                                            WinSmem<SMB, NPWv> &sm, bool partial) {
-    constexpr int H = MB * 16;
-    using S = WinSmem<SMB, NPWv>;
-    constexpr int NPW = S::NPW, NCH = S::NCH, TC = S::TC, BSTR = S::BSTR, KROWS = S::KROWS;
-    constexpr int PER = KROWS * NCH / 256;        // 16-byte staging chunks per thread
-    constexpr int RPP = 256 / NCH;                // B rows staged per pass
-    constexpr int NB = NPW / 16;                  // 16-column MFMA blocks of the panel
-    constexpr int NBW = (NB + 3) / 4;             // ... per wave (block wave + 4 nbi)
-    constexpr int U1 = MB == 1 ? 4 : 2;           // remainder entries per row gathered early
-    static_assert(MB <= SMB, "LDS sized for a smaller window");
-    static_assert(H * NPW * 4 <= KROWS * BSTR * 2, "C tile must fit in the B stage");
-    static_assert(TC <= 4, "wave w expands tile w of a round");
-    unsigned short *Bs = sm.Bs;
+// their parts in the workspace and arrive at the counter of (panel, slot,
+// share); the last arrival combines these rows (window_combine).  Owners skip
+// split rows, which the combine takes from the segments' partials.
+// BUF: B is reached through a buffer resource (a.b_rec; else plain loads).
+//
+// Bound by B rows arriving from L2 and beyond (latency at small grids).  One
+// workgroup per (window, panel of 128) with B in LDS, a barrier per 4 tiles
+// and tile values expanded from the bitmap took (us, before / now): a 32,768-row attention mask
+// (H = 64) at N = 256 of bf16 230 / 114 (4.5 GB of B rows, 0.8 PFLOP/s with
+// the tiles' zeros), 16,384 rows at N = 64 of f32 89 / 48, 3,001 rows at
+// N = 128 30 / 13; blocks of 262,144 rows (H = 16) at N = 256 of bf16 198 / 184.
+// Waves per SIMD a kernel of window items is compiled for: 128 accumulators
+// (in AGPRs) leave room for one, a single block fits three.
+template <int MBW, int CW>
+constexpr int window_waves() { return MBW * CW == 32 ? 1 : MBW == 1 ? 3 : 2; }
 
-    // owner items: (window in launch order, panel), tiles [t0, t0 + win_tmax);
-    // partial items: (partial slot, panel), tiles [wpart_t0, wpart_t1)
+template <int VT, int BT, int TT, int MB, int MBW, int CW, bool BUF, bool FUSED = false>
+__device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, int wid, bool partial) {
+    static_assert(MB == 0 ? MBW == 1 : MB % MBW == 0, "a wave takes whole 16-row blocks");
+    constexpr int NBUF = 2;
+    constexpr bool ACC = MBW * CW == 32;
+    constexpr int NPW = 16 * CW, SB = BT == DT_F32 ? 4 : 2;
+    constexpr bool PRE = MBW == 1;  // the rows' remainder ranges are loaded with the first tiles
+    const int H = MB ? MB * 16 : P.H;
+    const int subs_log2 = MB ? (MB / MBW == 4 ? 2 : MB / MBW == 2 ? 1 : 0) : (H >> 5);  // H 16, 32, 64
+    const int item = wid >> subs_log2, sub = wid & ((1 << subs_log2) - 1);
     const int j_item = item / a.win_panels, panel = item - j_item * a.win_panels;
     const int wi = partial ? P.wpart_win[j_item] : (P.win_order ? P.win_order[j_item] : j_item);
-    const int ncol0 = panel * NPW, ncols = min(NPW, P.n - ncol0);
-    const bool full = a.win_vec && ncols == NPW;  // every staging chunk is whole
-    const int tid = threadIdx.x, wave = wave_id(), lane = tid & 63;
-    const int g = lane >> 4, l16 = lane & 15;
+    const int ncol0 = panel_col<CW>(panel, NPW, P.n), ncols = min(NPW, P.n - ncol0);
+    const int lane = threadIdx.x & 63, g = lane >> 4, l16 = lane & 15;
     const int t0 = partial ? P.wpart_t0[j_item] : P.win_tile_ptr[wi];
     const int t1 = partial ? P.wpart_t1[j_item] : min(P.win_tile_ptr[wi + 1], t0 + P.win_tmax);
-    const int pa = partial ? 0 : P.win_part[wi], pb = partial ? 0 : P.win_part[wi + 1];
-    const int seg0 = partial ? 0 : P.win_seg[wi];  // first segment id of the window's rows
-    float *wpart = a.work + (int64_t)P.n_seg * a.work_ld;  // window partials follow the segments
+    const int start = ncol0 + min(l16 * CW, ncols - CW);  // this lane's columns start .. start + CW - 1
+    const bool own = l16 * CW < ncols;
+    const int rb0 = sub * MBW;
+    const __amdgpu_buffer_rsrc_t rs = b_resource(a.B, a.b_rec);
+    const uint32_t ldbs = (uint32_t)(a.ldb * SB), sbyte = (uint32_t)(start * SB);
+    const int64_t zoff = reinterpret_cast<const char *>(P.zeros) - static_cast<const char *>(a.B);
 
-    // window rows: lane `lane` of every wave holds row lane % H (wave 0 puts
-    // them in LDS), lane group `group` of wave `wave` owns row s1 of the first
-    // remainder pass
-    const Lanes L(a.win_lpr_log2);
-    const Lanes one = L.single();
-    const int s1 = wave * L.groups + L.group;
-    const int64_t wrow0 = (int64_t)(partial ? 0 : wi) * H;
-    const int rm = P.windows[wrow0 + (lane & (H - 1))];
-    const int r1 = P.windows[wrow0 + min(s1, H - 1)];
-
-    bool cok[CPL];
-    int64_t coff[CPL];
-    chunk_layout<E, CPL>(ncol0, ncols, L, cok, coff);
-    int col1[U1];
-    float val1[U1];
-    Raw<BT, E> g1[U1][CPL];
-    int b1 = 0, e1 = 0;
-
-    f32x4 acc[MB][NBW];
+    // chunks of 8 B rows at this lane's columns; zeros where col < 0
+    auto load_rows = [&](const int (&col)[8], Chunk<BT, CW> (&x)[8]) {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int j = 0; j < NBW; ++j) acc[mb][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-
-    // level 2 of a round: the tile columns of this thread's staging chunks,
-    // and the bitmap words and value offsets of the tile this wave expands
-    // (wave w expands tile w of the round).  The next round's are loaded
-    // alongside this round's staging loads, so a round after the first
-    // starts with its tile values and B rows.
-    struct RoundMeta {
-        int colr[PER];
-        uint32_t wrd[MB];
-        int tv, vend;
-    };
-    auto fetch_meta = [&](int tc0, RoundMeta &m) {
-        const int nt = min(TC, t1 - tc0);
-#pragma unroll
-        for (int it = 0; it < PER; ++it) {
-            const int kr = (tid + it * 256) / NCH;
-            const int c = P.tile_cols[(int64_t)tc0 * 32 + min(kr, nt * 32 - 1)];
-            m.colr[it] = kr < nt * 32 ? c : -1;
-        }
-        const int wv = min(wave, nt - 1);
-        m.vend = P.tile_val_ptr[tc0 + nt];
-        m.tv = P.tile_val_ptr[tc0 + wv];
-#pragma unroll
-        for (int rp = 0; rp < MB; ++rp) m.wrd[rp] = P.tile_bitmap[(int64_t)(tc0 + wv) * H + rp * 16 + (lane >> 2)];
-    };
-
-    auto round = [&](auto first_tag, int tc0, const RoundMeta &m, RoundMeta &next) {
-        constexpr bool FIRST = decltype(first_tag)::value;
-        const int nt = min(TC, t1 - tc0);
-        const int(&colr)[PER] = m.colr;
-        const uint32_t(&wrd)[MB] = m.wrd;
-        const int tv = m.tv, vend = m.vend;
-        // lane (r, q) = (lane / 4, lane % 4) of wave w takes columns
-        // 8q .. 8q+7 of rows r, r + 16, .. of tile w
-        const int q4 = lane & 3;
-        int bm_ = 0, em_ = 0;
-        if constexpr (FIRST) {
-            bm_ = P.rem_ptr[max(rm, 0)];
-            em_ = P.rem_ptr[max(rm, 0) + 1];
-            b1 = P.rem_ptr[max(r1, 0)];
-            e1 = P.rem_ptr[max(r1, 0) + 1];
-        }
-        // level 3: tile values, remainder entries, B rows of the staging chunks.
-        // A row's values follow those of the tile's earlier rows (prefix over
-        // the 16-row passes by a wave scan) and, inside the row, the bitmap
-        // order; every load is issued at a clamped index and masked after.
-        uint32_t av[MB][4];
-        {
-            int carry = 0;
-#pragma unroll
-            for (int rp = 0; rp < MB; ++rp) {
-                const uint32_t word = wrd[rp], mine = (word >> (8 * q4)) & 0xFFu;
-                const int pc = __popc(word);
-                const int incl = wave_inclusive_scan(q4 == 0 ? pc : 0);
-                const int base = tv + carry + incl - pc + __popc(word & ((1u << (8 * q4)) - 1u));
-                carry += __shfl(incl, 63, 64);
-                // this lane's values are consecutive in the packed order:
-                // one (2-byte aligned) 16-byte load at `base` holds them (the
-                // plan's arrays end in at least 16 zero bytes), then set bit
-                // i takes the next value in turn
-                u32x4 raw;
-                __builtin_memcpy(&raw, P.tile_vals + max(min(base, vend), 0), 16);
-                uint64_t lo = (uint64_t)raw[0] | ((uint64_t)raw[1] << 32);
-                uint64_t hi = (uint64_t)raw[2] | ((uint64_t)raw[3] << 32);
-                unsigned short x[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const bool set = (mine >> i) & 1u;
-                    x[i] = set ? (unsigned short)(lo & 0xFFFFu) : (unsigned short)0;
-                    const uint64_t nlo = (lo >> 16) | (hi << 48), nhi = hi >> 16;
-                    lo = set ? nlo : lo;
-                    hi = set ? nhi : hi;
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) av[rp][i] = (uint32_t)x[2 * i] | ((uint32_t)x[2 * i + 1] << 16);
-            }
-        }
-        bool live1 = false, split1 = false;
-        int q1 = 0;
-        if constexpr (FIRST) {
-            live1 = !partial && s1 < H && r1 >= 0;
-            split1 = e1 - b1 > P.seg_len;
-            q1 = live1 && !split1 ? e1 : b1;  // end of the entries gathered here
-            // indices clamped into [0, q1 - 1] (the plan arrays carry a zero
-            // tail for an empty range); entries at and beyond q1 are not used
-#pragma unroll
-            for (int u = 0; u < U1; ++u) {
-                const int pp = max(min(b1 + u, q1 - 1), 0);
-                col1[u] = __builtin_nontemporal_load(P.rem_col + pp);
-                val1[u] = load_val<VT>(P.rem_val, pp);
-            }
-        }
-        // B rows of the staging chunks: thread tid stages, in pass it, row
-        // kr = RPP it + tid / NCH into LDS bytes [4096 it + 16 tid, +16), i.e.
-        // slot tid % NCH of that row, which holds chunk (tid % NCH) ^ bswz(kr)
-        if constexpr (BT != DT_F32) {
-            if (full) {
-                // one direct global-to-LDS load per pass and wave; chunks
-                // without a column (tile padding, rows beyond the round) read
-                // the plan's zero block
-#pragma unroll
-                for (int it = 0; it < PER; ++it) {
-                    const int kr = RPP * it + tid / NCH, cg = (tid & (NCH - 1)) ^ bswz<NCH>(kr);
-                    const unsigned short *src =
-                        colr[it] >= 0 ? static_cast<const unsigned short *>(a.B) +
-                                            (int64_t)colr[it] * a.ldb + ncol0 + cg * 8
-                                      : P.zeros;
-                    __builtin_amdgcn_global_load_lds(
-                        src, (__attribute__((address_space(3))) void *)(Bs + it * 2048 + wave * 512), 16, 0,
-                        0);
-                }
+        for (int i = 0; i < 8; ++i) {
+            if constexpr (BUF) {
+                x[i].load(rs, (uint32_t)col[i] * ldbs + sbyte);  // -1: wraps to beyond the resource
             } else {
-#pragma unroll
-                for (int it = 0; it < PER; ++it) {
-                    const int kr = RPP * it + tid / NCH, cg = (tid & (NCH - 1)) ^ bswz<NCH>(kr);
-                    uint32_t w[4] = {0u, 0u, 0u, 0u};
-                    const int valid = min(8, ncols - cg * 8);
-                    if (colr[it] >= 0 && valid > 0)
-                        stage_b8<BT, TT>(a.B, (int64_t)colr[it] * a.ldb + ncol0 + cg * 8, valid, a.win_vec, w);
-                    *reinterpret_cast<u32x4 *>(&Bs[it * 2048 + tid * 8]) = u32x4{w[0], w[1], w[2], w[3]};
-                }
-            }
-        } else {
-            // f32 B, converted to bf16: two passes' loads in flight at a time
-#pragma unroll
-            for (int h = 0; h < PER; h += 2) {
-                uint32_t w[2][4];
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const int it = h + q, kr = RPP * it + tid / NCH, cg = (tid & (NCH - 1)) ^ bswz<NCH>(kr);
-                    w[q][0] = w[q][1] = w[q][2] = w[q][3] = 0u;
-                    const int valid = min(8, ncols - cg * 8);
-                    if (full) {
-                        const float *b = static_cast<const float *>(a.B) +
-                                         (int64_t)max(colr[it], 0) * a.ldb + ncol0 + cg * 8;
-                        const f32x4 x0 = *reinterpret_cast<const f32x4 *>(b);
-                        const f32x4 x1 = *reinterpret_cast<const f32x4 *>(b + 4);
-                        const bool ok = colr[it] >= 0;
-                        w[q][0] = ok ? (f32_to_bf16_bits(x0[0]) | (f32_to_bf16_bits(x0[1]) << 16)) : 0u;
-                        w[q][1] = ok ? (f32_to_bf16_bits(x0[2]) | (f32_to_bf16_bits(x0[3]) << 16)) : 0u;
-                        w[q][2] = ok ? (f32_to_bf16_bits(x1[0]) | (f32_to_bf16_bits(x1[1]) << 16)) : 0u;
-                        w[q][3] = ok ? (f32_to_bf16_bits(x1[2]) | (f32_to_bf16_bits(x1[3]) << 16)) : 0u;
-                    } else if (colr[it] >= 0 && valid > 0) {
-                        stage_b8<BT, TT>(a.B, (int64_t)colr[it] * a.ldb + ncol0 + cg * 8, valid, a.win_vec,
-                                         w[q]);
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-                    *reinterpret_cast<u32x4 *>(&Bs[(h + q) * 2048 + tid * 8]) =
-                        u32x4{w[q][0], w[q][1], w[q][2], w[q][3]};
+                const int64_t off = ((int64_t)col[i] * a.ldb + start) * SB;
+                x[i].load(static_cast<const char *>(a.B) + (col[i] >= 0 ? off : zoff));
             }
         }
-        // the next round's level 2, in flight with this round's staging
-        if (tc0 + TC < t1) fetch_meta(tc0 + TC, next);
-        // LDS: expanded tiles (tile w, row r, columns 8q ..: 16 bytes at
-        // ((w H + r) 32 + 8q) elements), row metadata
-        if (wave < nt) {
-#pragma unroll
-            for (int rp = 0; rp < MB; ++rp)
-                *reinterpret_cast<u32x4 *>(&sm.As[((wave * H + rp * 16 + (lane >> 2)) * 32) + 8 * q4]) =
-                    u32x4{av[rp][0], av[rp][1], av[rp][2], av[rp][3]};
-        }
-        if constexpr (FIRST) {
-            if (wave == 0 && !partial) {
-                // the window's rows, their remainder ranges and segment ids
-                const bool own = lane < H && rm >= 0;
-                const int len = own ? em_ - bm_ : 0;
-                const int ns = len > P.seg_len ? (len + P.seg_len - 1) / P.seg_len : 0;
-                const int x = wave_inclusive_scan(ns);
-                if (lane < H) {
-                    sm.rows[lane] = rm;
-                    sm.rb[lane] = bm_;
-                    sm.re[lane] = em_;
-                    sm.sid[lane] = seg0 + x - ns;
-                }
-            }
-        }
-        __syncthreads();
-        if constexpr (FIRST) {
-            // level 4: the early remainder entries' B rows (a valid row for
-            // unused entries and chunks outside the panel), issued after the
-            // barrier (which waits for the staging loads) and consumed after
-            // the MFMA rounds
-#pragma unroll
-            for (int u = 0; u < U1; ++u)
-#pragma unroll
-                for (int c = 0; c < CPL; ++c)
-                    load_raw<BT, E, false>(a.B, (int64_t)(col1[u] & 0x7FFFFFFF) * a.ldb + coff[c], g1[u][c]);
-        }
-        for (int j = 0; j < nt; ++j) {
-            // A operand: lane (g, m) takes row m, columns 8g .. 8g+7 of tile j
-            u16x8 af[MB];
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-                af[mb] = *reinterpret_cast<const u16x8 *>(&sm.As[((j * H + mb * 16 + l16) * 32) + 8 * g]);
-#pragma unroll
-            for (int nbi = 0; nbi < NBW; ++nbi) {
-                const int nb = wave + 4 * nbi;
-                if (NB < 4 && nb >= NB) continue;  // narrow panels: waves without a block
-                // B operand: lane (g, n) needs rows 8g .. 8g+7 of column n.
-                // ds_read_b64_tr_b16 transposes within each 16-lane block:
-                // lane a of the block reads 4 consecutive columns of one row,
-                // and lane n receives element i from lane 4i + n/4, column
-                // n % 4; so lane a reads row 4h + a/4, columns 4(a % 4) ..
-                u16x8 bf;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int k = j * 32 + 8 * g + 4 * h + (l16 >> 2), n0 = nb * 16 + 4 * (l16 & 3);
-                    const v4i16 t = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                        (__attribute__((address_space(3))) v4i16 *)(Bs + k * BSTR +
-                                                                    (((n0 >> 3) ^ bswz<NCH>(k)) << 3) + (n0 & 7)));
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) bf[4 * h + i] = (unsigned short)t[i];
-                }
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb) acc[mb][nbi] = mfma_16x16x32<TT>(af[mb], bf, acc[mb][nbi]);
-            }
-        }
-        return q1;
     };
-    // a valid plan gives every window and partial item at least one tile
-    RoundMeta cur, nxt;
-    fetch_meta(t0, cur);
-    const int q1 = round(std::true_type{}, t0, cur, nxt);
-    for (int tc0 = t0 + TC; tc0 < t1; tc0 += TC) {
-        __syncthreads();  // the previous round's LDS reads are done
-        cur = nxt;
-        (void)round(std::false_type{}, tc0, cur, nxt);
+
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    // rows 16 (rb0 + mb) + 4g .. + 3 of the window: id and remainder range
+    struct Rows {
+        i32x4 r;
+        int b[4], e[4];
+    };
+    auto row_ids = [&](int mb, Rows &R) {
+        R.r = *reinterpret_cast<const i32x4 *>(P.windows + (int64_t)wi * H + (rb0 + mb) * 16 + 4 * g);
+    };
+    auto row_ranges = [&](Rows &R) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            R.b[x] = P.rem_ptr[max(R.r[x], 0)];
+            R.e[x] = P.rem_ptr[max(R.r[x], 0) + 1];
+        }
+    };
+    auto split = [&](const Rows &R, int x) { return R.r[x] >= 0 && R.e[x] - R.b[x] > P.seg_len; };
+    // end of the entries gathered here: none of a missing or a split row
+    auto end = [&](const Rows &R, int x) { return R.r[x] < 0 || R.e[x] - R.b[x] > P.seg_len ? R.b[x] : R.e[x]; };
+    // entries u .. u + 15 of each of the 4 rows, one a lane of the row's group
+    // (at clamped indices: the plan's arrays end in zeros)
+    struct Entries {
+        int col[4];
+        float v[4];
+    };
+    auto entries = [&](const Rows &R, int u, Entries &q) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int p = max(min(R.b[x] + u + l16, end(R, x) - 1), 0);
+            q.col[x] = __builtin_nontemporal_load(P.rem_col + p) & 0x7FFFFFFF;
+            q.v[x] = load_val<VT>(P.rem_val, p);
+        }
+    };
+    // whether row x has an entry u, and its column (-1 without it) and value,
+    // from lane u % 16 of the group
+    auto has = [&](const Rows &R, int x, int u) { return R.b[x] + u < end(R, x); };
+    auto from = [&](int v, int u) { return __builtin_amdgcn_ds_bpermute(((lane & 48) | (u & 15)) << 2, v); };
+
+    Rows R;
+    Entries q0;
+    bool some = false;  // any of the rows has an entry to gather
+
+    struct Buf {
+        Chunk<BT, CW> b[8];
+        u32x4 a[MBW];
+    };
+    // tile column 8g + lane % 8 of tile t (of the last past the end)
+    auto fetch = [&](int t) { return (P.tile_cols + (int64_t)min(t, t1 - 1) * 32)[8 * g + (lane & 7)]; };
+    // (the scheduling barriers keep a buffer's loads behind the multiplication
+    // that frees it: moved up, they take another buffer's registers)
+    // (REM: past the last tile the remainder's rows instead)
+    auto issue = [&](int t, int c, Buf &x, auto rem_tag) {
+        constexpr bool REM = decltype(rem_tag)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        if (!REM && t >= t1) c = -1;
+        const uint16_t *v = P.tile_dense + ((int64_t)(t < t1 ? t : P.n_tiles) * H + rb0 * 16) * 32;
+#pragma unroll
+        for (int mb = 0; mb < MBW; ++mb) x.a[mb] = *reinterpret_cast<const u32x4 *>(v + (mb * 16 + l16) * 32 + 8 * g);
+        int col[8] = {row16_broadcast<0>(c), row16_broadcast<1>(c), row16_broadcast<2>(c), row16_broadcast<3>(c),
+                      row16_broadcast<4>(c), row16_broadcast<5>(c), row16_broadcast<6>(c), row16_broadcast<7>(c)};
+        if constexpr (REM) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {  // entries 0 and 1 of every row
+                const int x = i >> 1, c = i & 1 ? row16_broadcast<1>(q0.col[x]) : row16_broadcast<0>(q0.col[x]);
+                col[i] = t < t1 ? col[i] : some && has(R, x, i & 1) ? c : -1;
+            }
+        }
+        load_rows(col, x.b);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    f32x4 acc[MBW][CW];
+#pragma unroll
+    for (int mb = 0; mb < MBW; ++mb)
+#pragma unroll
+        for (int i = 0; i < CW; ++i) acc[mb][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto multiply = [&](const Buf &x) {
+#pragma unroll
+        for (int i = 0; i < CW; ++i) {
+            u32x4 bf;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const Chunk<BT, CW> &lo = x.b[2 * p], &hi = x.b[2 * p + 1];
+                if constexpr (BT == DT_F32) bf[p] = pack_bf16(lo.f32(i), hi.f32(i));
+                else bf[p] = __builtin_amdgcn_perm(hi.w[i >> 1], lo.w[i >> 1], i & 1 ? 0x07060302u : 0x05040100u);
+            }
+#pragma unroll
+            for (int mb = 0; mb < MBW; ++mb) {
+                if constexpr (ACC) {
+                    if constexpr (TT == DT_BF16)
+                        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[mb][i]) : "v"(x.a[mb]), "v"(bf));
+                    else
+                        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc[mb][i]) : "v"(x.a[mb]), "v"(bf));
+                } else {
+                    acc[mb][i] = mfma_16x16x32<TT>(x.a[mb], bf, acc[mb][i]);
+                }
+            }
+            if (i & 1) __builtin_amdgcn_sched_barrier(0);  // two operands at a time
+        }
+    };
+
+    const std::false_type tiles;
+    int m[NBUF];
+    Buf x[NBUF];
+    if (PRE && !partial) row_ids(0, R);
+#pragma unroll
+    for (int i = 0; i < NBUF; ++i) m[i] = fetch(t0 + i);
+    if (PRE && !partial) row_ranges(R);
+#pragma unroll
+    for (int i = 0; i < NBUF; ++i) {
+        issue(t0 + i, m[i], x[i], tiles);
+        m[i] = fetch(t0 + NBUF + i);
     }
-    // fused: the window's slot when its result needs other items' parts
+    if constexpr (PRE) {
+        bool any = false;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) any |= !partial && has(R, x, 0);
+        some = __any(any);
+        if (some) entries(R, 0, q0);
+    }
+    for (int t = t0; t < t1; t += NBUF) {
+        // (the first buffer's last issue is not multiplied any more)
+        multiply(x[0]);
+        issue(t + NBUF, m[0], x[0], std::integral_constant<bool, PRE>{});
+        m[0] = fetch(t + 2 * NBUF);
+#pragma unroll
+        for (int i = 1; i < NBUF; ++i) {
+            multiply(x[i]);
+            issue(t + NBUF + i, m[i], x[i], tiles);
+            m[i] = fetch(t + 2 * NBUF + i);
+        }
+    }
+    if constexpr (ACC) {
+#pragma unroll
+        for (int mb = 0; mb < MBW; ++mb)
+#pragma unroll
+            for (int i = 0; i < CW; ++i) asm volatile("s_nop 15\n\ts_nop 7" : "+a"(acc[mb][i]));
+    }
+
+    const int64_t ld = a.work_ld;
+    const __amdgpu_buffer_rsrc_t ws = ws_resource(a);
     const int dep = FUSED ? P.win_dep[wi] : -1;
+    // CW columns of a workspace row that other workgroups of this launch read
+    auto st_ws = [&](int64_t off, const float (&z)[CW]) {
+#pragma unroll
+        for (int c = 0; c < CW; c += CW >= 4 ? 4 : 1) {
+            if constexpr (CW >= 4) st_dev_chunk<4>(ws, off + c, *reinterpret_cast<const float(*)[4]>(&z[c]));
+            else st_dev1(ws, off + c, z[c]);
+        }
+    };
     if (partial || dep >= 0) {
         // the MFMA result of these tiles: for the owner item (or the last
         // arrival) to add, or the owner's own, kept in the window's slot
-        float *dst = (partial ? wpart + (int64_t)j_item * H * a.work_ld
-                              : a.dep + (int64_t)dep * 2 * H * a.work_ld) + ncol0;
+        const int64_t dst = partial ? (int64_t)P.n_seg * ld + (int64_t)j_item * H * ld
+                                    : (a.dep - a.work) + (int64_t)dep * 2 * H * ld;
+        if (own) {
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+            for (int mb = 0; mb < MBW; ++mb)
 #pragma unroll
-            for (int nbi = 0; nbi < NBW; ++nbi) {
-                const int col = (wave + 4 * nbi) * 16 + l16;
-                if (wave + 4 * nbi < NB && col < ncols) {
+                for (int x = 0; x < 4; ++x) {
+                    float z[CW];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        float *d = dst + (int64_t)(mb * 16 + 4 * g + i) * a.work_ld + col;
-                        if constexpr (FUSED) st_dev1(ws_resource(a), d - a.work, acc[mb][nbi][i]);
-                        else *d = acc[mb][nbi][i];
+                    for (int c = 0; c < CW; ++c) z[c] = acc[mb][c][x];
+                    const int64_t off = dst + (int64_t)((rb0 + mb) * 16 + 4 * g + x) * ld + start;
+                    if constexpr (FUSED) {
+                        st_ws(off, z);
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < CW; ++c) a.work[off + c] = z[c];
                     }
                 }
-            }
+        }
         if (partial) {
             if constexpr (FUSED) {
-                if (group_arrive(win_counter(P, a, panel, dep), win_target(P, a, wi, panel), &sm.flag))
-                    window_combine(P, a, wi, panel, dep, tid, 256);
+                if (wave_arrive(win_counter(P, a, panel, dep, sub), win_target(P, a, wi, panel)))
+                    window_combine<MBW == 1 ? 4 : 8>(P, a, wi, panel, dep, sub);
             }
             return;
         }
     }
-    // the first pass's rows: their early entries, then the rest in order
-    float v1[CPL][E];
-#pragma unroll
-    for (int c = 0; c < CPL; ++c)
-#pragma unroll
-        for (int x = 0; x < E; ++x) v1[c][x] = 0.0f;
-    fma_rows<BT, E, CPL, U1>(val1, g1, b1, q1, one, v1);
-    if (q1 > b1 + U1)
-        row_accumulate_group<VT, BT, E, CPL, unroll_of<E, CPL>()>(
-            P.rem_col, P.rem_val, b1 + U1, q1, a.B, a.ldb, a.b_rec, ncol0, ncols, L, a.cold_aux, v1);
-    __syncthreads();
-    float *Cs = reinterpret_cast<float *>(Bs);
-    if (dep < 0) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int nbi = 0; nbi < NBW; ++nbi)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (wave + 4 * nbi < NB)
-                        Cs[(mb * 16 + 4 * g + i) * NPW + (wave + 4 * nbi) * 16 + l16] = acc[mb][nbi][i];
-    }
-    // add the partial results of the window's other tiles, in tile order
-    // (fused: a window with partial items has a slot, combined at the end)
-    if (!FUSED && pb > pa) {
-        __syncthreads();
-        for (int x = tid; x < H * NPW; x += 256) {
-            const int srow = x / NPW, col = x - srow * NPW;
-            if (col < ncols) {
-                float v = Cs[x];
-                for (int k = pa; k < pb; ++k)
-                    v += wpart[((int64_t)k * H + srow) * a.work_ld + ncol0 + col];
-                Cs[x] = v;
-            }
-        }
-    }
-    __syncthreads();
 
-    // Remainders: every lane group takes its own row of the window, so up to
-    // 4 * G rows progress at once; a row's entries are summed in order by its
-    // group.  Rows then add the tile result and are written once.
-    for (int s0 = 0; s0 < H; s0 += 4 * L.groups) {
-        const int s = s0 + s1;
-        const int r = s < H ? sm.rows[s] : -1;
-        float v[CPL][E];
 #pragma unroll
-        for (int c = 0; c < CPL; ++c)
+    for (int mb = 0; mb < MBW; ++mb) {
+        float v[4][CW];
 #pragma unroll
-            for (int x = 0; x < E; ++x) v[c][x] = s0 == 0 ? v1[c][x] : 0.0f;
-        if (r >= 0) {
-            const int b = sm.rb[s], e = sm.re[s];
-            const bool split = e - b > P.seg_len;
-            if (split) {
-                // fused: only windows with a slot have split rows; the
-                // combine sums their segment partials
-                if constexpr (!FUSED) {
-                    const int ns = (e - b + P.seg_len - 1) / P.seg_len;
-                    sum_partials<E, CPL>(a.work, a.work_ld, sm.sid[s], ns, ncol0, ncols, L, v);
-                }
-            } else if (s0 != 0) {
-                row_accumulate_group<VT, BT, E, CPL, unroll_of<E, CPL>()>(
-                    P.rem_col, P.rem_val, b, e, a.B, a.ldb, a.b_rec, ncol0, ncols, L, a.cold_aux, v);
-            }
-            if (dep >= 0) {
-                // the row's remainder, for the combine
-                if (!split) {
-                    const int64_t rm = (a.dep - a.work) + ((int64_t)dep * 2 + 1) * H * a.work_ld +
-                                       (int64_t)s * a.work_ld + ncol0;
+        for (int x = 0; x < 4; ++x)
 #pragma unroll
-                    for (int c = 0; c < CPL; ++c) {
-                        const int q = c * L.lpr + L.li;
-                        if (q * E < ncols) st_dev_chunk<E>(ws_resource(a), rm + (int64_t)q * E, v[c]);
+            for (int c = 0; c < CW; ++c) v[x][c] = 0.0f;
+        int u = 0;
+        if constexpr (PRE) {
+            if (some) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int r = i >> 1, k = __float_as_int(q0.v[r]);
+                    const float val = __int_as_float(i & 1 ? row16_broadcast<1>(k) : row16_broadcast<0>(k));
+                    if (has(R, r, i & 1)) {
+#pragma unroll
+                        for (int c = 0; c < CW; ++c) v[r][c] = __builtin_fmaf(val, x[0].b[i].f32(c), v[r][c]);
                     }
                 }
+                u = 2;
+            }
+        } else {
+            row_ids(mb, R);
+            row_ranges(R);
+        }
+        auto more = [&] {
+            bool any = false;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) any |= has(R, r, u);
+            return __any(any);
+        };
+        // the rest, RE entries of every row at a time, the next 16 entries in
+        // flight with the last of these.  4 entries, 2 where their chunks would
+        // spill: 64 registers of chunks for any width (16 entries at 32 columns)
+        // cost 38,624 rows in blocks (2.2 entries a row), N = 32, 18.8 us for 8.1.
+        constexpr int RE = MBW == 1 && CW == 8 ? 2 : 4;
+        if (more()) {
+            if (!PRE) entries(R, 0, q0);
+            do {
+                Chunk<BT, CW> rows[RE / 2][8];
+                float val[4 * RE];
+                const int u0 = u;
+#pragma unroll
+                for (int i = 0; i < RE / 2; ++i) {
+                    int col[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const int r = (8 * i + k) / RE, w = u0 + (8 * i + k) % RE;
+                        const int c = from(q0.col[r], w);
+                        col[k] = has(R, r, w) && w < (u0 | 15) + 1 ? c : -1;
+                        val[8 * i + k] = __int_as_float(from(__float_as_int(q0.v[r]), w));
+                    }
+                    load_rows(col, rows[i]);
+                }
+                const int u1 = min(u0 + RE, (u0 | 15) + 1);  // (not past the 16 entries held)
+                u = u1;
+                if ((u1 & 15) == 0) entries(R, u1, q0);
+#pragma unroll
+                for (int i = 0; i < 4 * RE; ++i) {
+                    const int r = i / RE, w = u0 + i % RE;
+                    if (w < u1 && has(R, r, w)) {
+#pragma unroll
+                        for (int c = 0; c < CW; ++c)
+                            v[r][c] = __builtin_fmaf(val[i], rows[i >> 3][i & 7].f32(c), v[r][c]);
+                    }
+                }
+            } while (more());
+        }
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int s = (rb0 + mb) * 16 + 4 * g + x;
+            if (R.r[x] < 0 || !own) continue;
+            if (dep >= 0) {
+                // the row's remainder, for the combine (a split row's is
+                // summed there from its segments' partials)
+                if (!split(R, x)) st_ws((a.dep - a.work) + ((int64_t)dep * 2 + 1) * H * ld + (int64_t)s * ld + start, v[x]);
+                continue;
+            }
+            float z[CW];
+#pragma unroll
+            for (int c = 0; c < CW; ++c) z[c] = acc[mb][c][x];
+            if constexpr (!FUSED) {
+                // the window's other tiles' partial results, in tile order
+                // (fused: a window with partial items has a slot)
+                for (int k = P.win_part[wi]; k < P.win_part[wi + 1]; ++k) {
+                    const float *w = a.work + ((int64_t)P.n_seg + (int64_t)k * H + s) * ld + start;
+#pragma unroll
+                    for (int c = 0; c < CW; ++c) z[c] += w[c];
+                }
+                if (split(R, x)) {  // its segments' partials, in segment order
+                    const int sid = P.win_row_sid[(int64_t)wi * H + s];
+                    const int ns = (R.e[x] - R.b[x] + P.seg_len - 1) / P.seg_len;
+                    for (int k = 0; k < ns; ++k) {
+                        const float *w = a.work + (int64_t)(sid + k) * ld + start;
+#pragma unroll
+                        for (int c = 0; c < CW; ++c) v[x][c] = k ? v[x][c] + w[c] : w[c];
+                    }
+                }
+            }
+            float *dst = a.C + (int64_t)R.r[x] * a.ldc + start;
+#pragma unroll
+            for (int c = 0; c < CW; ++c) z[c] = z[c] + v[x][c];
+            if constexpr (CW >= 4) {
+#pragma unroll
+                for (int c = 0; c < CW; c += 4)
+                    __builtin_nontemporal_store(f32x4e{z[c], z[c + 1], z[c + 2], z[c + 3]},
+                                                reinterpret_cast<f32x4e *>(dst + c));
             } else {
 #pragma unroll
-                for (int c = 0; c < CPL; ++c) {
-                    const int q = c * L.lpr + L.li;
-                    if (q * E < ncols) {
-#pragma unroll
-                        for (int x = 0; x < E; ++x) v[c][x] = Cs[s * NPW + q * E + x] + v[c][x];
-                        store_chunk<E>(a.C, (int64_t)r * a.ldc + ncol0 + (int64_t)q * E, v[c]);
-                    }
-                }
+                for (int c = 0; c < CW; ++c) __builtin_nontemporal_store(z[c], dst + c);
             }
         }
     }
     if constexpr (FUSED) {
-        if (dep >= 0 && group_arrive(win_counter(P, a, panel, dep), win_target(P, a, wi, panel), &sm.flag))
-            window_combine(P, a, wi, panel, dep, tid, 256);
+        if (dep >= 0 && wave_arrive(win_counter(P, a, panel, dep, sub), win_target(P, a, wi, panel)))
+            window_combine<MBW == 1 ? 4 : 8>(P, a, wi, panel, dep, sub);
     }
 }
 }  // namespace spmm

@@ -19,20 +19,11 @@ __global__ __launch_bounds__(256) void vector_kernel(DevPlan P, RunArgs a) {
 }
 
 
-template <int VT, int BT, int TT, int MB, int E, int CPL, int NPW>
-__global__ __launch_bounds__(256) void window_kernel(DevPlan P, RunArgs a) {
-    __shared__ WinSmem<MB, NPW> sm;
-    const int item = logical_block(a.xcd);
-    if (item < P.n_win * a.win_panels)
-        window_item<VT, BT, TT, MB, E, CPL, MB, false, NPW>(P, a, item, sm, false);
-}
-
-template <int VT, int BT, int TT, int MB, int E, int CPL, int NPW>
-__global__ __launch_bounds__(256) void window_partial_kernel(DevPlan P, RunArgs a) {
-    __shared__ WinSmem<MB, NPW> sm;
-    const int item = logical_block(a.xcd);
-    if (item < P.n_wpart * a.win_panels)
-        window_item<VT, BT, TT, MB, E, CPL, MB, false, NPW>(P, a, item, sm, true);
+template <int VT, int BT, int TT, int MB, int MBW, int CW, bool BUF>
+__global__ __launch_bounds__(256, (window_waves<MBW, CW>())) void window_kernel(DevPlan P, RunArgs a, int partial) {
+    const int wid = logical_block(a.xcd) * 4 + wave_id();
+    if (wid < (partial ? P.n_wpart : P.n_win) * a.win_panels * a.win_subs)
+        window_item<VT, BT, TT, MB, MBW, CW, BUF>(P, a, wid, partial != 0);
 }
 
 
@@ -82,29 +73,27 @@ __global__ __launch_bounds__(256) void batch_vector_kernel(const BatchHeader *__
                   (vector_item_var<VT, BT, E, CPL, VAR, false, batch_unroll<E, CPL>()>(tab[d].P, tab[d].a, item)));
 }
 
-template <int VT, int BT, int TT, int E, int CPL, int MB>
-__device__ __forceinline__ void window_item_h(const BatchEntry &e, int item, WinSmem<4> &sm,
-                                              bool partial) {
-    window_item<VT, BT, TT, MB, E, CPL, 4>(e.P, e.a, item, sm, partial);
-    __syncthreads();  // the next item reuses the LDS
+template <int VT, int BT, int TT, bool PARTIAL>
+__device__ __forceinline__ void batch_window_item(const BatchEntry &e, int wid) {
+    if constexpr (BT != DT_F32)
+        if (e.a.win_np == 128)
+            return e.a.b_rec ? window_item<VT, BT, TT, 0, 1, 8, true>(e.P, e.a, wid, PARTIAL)
+                             : window_item<VT, BT, TT, 0, 1, 8, false>(e.P, e.a, wid, PARTIAL);
+    if (e.a.win_np == 64)
+        return e.a.b_rec ? window_item<VT, BT, TT, 0, 1, 4, true>(e.P, e.a, wid, PARTIAL)
+                         : window_item<VT, BT, TT, 0, 1, 4, false>(e.P, e.a, wid, PARTIAL);
+    if (e.a.win_np == 32)
+        return e.a.b_rec ? window_item<VT, BT, TT, 0, 1, 2, true>(e.P, e.a, wid, PARTIAL)
+                         : window_item<VT, BT, TT, 0, 1, 2, false>(e.P, e.a, wid, PARTIAL);
+    window_item<VT, BT, TT, 0, 1, 1, false>(e.P, e.a, wid, PARTIAL);
 }
 
-template <int VT, int BT, int TT, int E, int CPL, bool PARTIAL>
-__global__ __launch_bounds__(256) void batch_window_kernel(const BatchHeader *__restrict__ hdr,
+template <int VT, int BT, int TT, bool PARTIAL>
+__global__ __launch_bounds__(256, 2) void batch_window_kernel(const BatchHeader *__restrict__ hdr,
                                                            const BatchEntry *__restrict__ tab) {
-    __shared__ WinSmem<4> sm;
-    const int sub = 0;
-    if (PARTIAL) {
-        SPMM_XCD_WALK(x_wpart, wpart_end, wpart_base, 1,
-                      (tab[d].P.H == 16 ? window_item_h<VT, BT, TT, E, CPL, 1>(tab[d], item, sm, true)
-                       : tab[d].P.H == 32 ? window_item_h<VT, BT, TT, E, CPL, 2>(tab[d], item, sm, true)
-                                          : window_item_h<VT, BT, TT, E, CPL, 4>(tab[d], item, sm, true)));
-    } else {
-        SPMM_XCD_WALK(x_win, win_end, win_base, 1,
-                      (tab[d].P.H == 16 ? window_item_h<VT, BT, TT, E, CPL, 1>(tab[d], item, sm, false)
-                       : tab[d].P.H == 32 ? window_item_h<VT, BT, TT, E, CPL, 2>(tab[d], item, sm, false)
-                                          : window_item_h<VT, BT, TT, E, CPL, 4>(tab[d], item, sm, false)));
-    }
+    const int sub = wave_id();
+    if (PARTIAL) SPMM_XCD_WALK(x_wpart, wpart_end, wpart_base, 4, (batch_window_item<VT, BT, TT, true>(tab[d], item)));
+    else SPMM_XCD_WALK(x_win, win_end, win_base, 4, (batch_window_item<VT, BT, TT, false>(tab[d], item)));
 }
 
 // Streaming copy used as the achievable-bandwidth reference: one 16-byte
@@ -171,41 +160,14 @@ static hipError_t vec_dispatch(const DevPlan &P, const RunArgs &a, hipStream_t s
 
 template <int VT, int BT, int TT>
 static hipError_t win_dispatch(const DevPlan &P, const RunArgs &a, hipStream_t s, bool partial) {
-    const int64_t wgs = (int64_t)(partial ? P.n_wpart : P.n_win) * a.win_panels;
-    if (wgs == 0) return hipSuccess;
-    constexpr int EV = BT == DT_F32 ? 4 : 8;
-    dim3 grid((unsigned)wgs), block(256);
-#define SPMM_WIN_NP(MB, NP)                                                                          \
-    do {                                                                                             \
-        if (partial)                                                                                 \
-            launch_kernel((window_partial_kernel<VT, BT, TT, MB, EV, 1, NP>), grid, block, 0, s, P, a); \
-        else                                                                                         \
-            launch_kernel((window_kernel<VT, BT, TT, MB, EV, 1, NP>), grid, block, 0, s, P, a);  \
-    } while (0)
-#define SPMM_WIN(MB)                                                                                 \
-    do {                                                                                             \
-        if (!a.win_vec) {                                                                            \
-            if (partial)                                                                             \
-                launch_kernel((window_partial_kernel<VT, BT, TT, MB, 1, 2, 128>), grid, block, 0, s, P, a); \
-            else                                                                                     \
-                launch_kernel((window_kernel<VT, BT, TT, MB, 1, 2, 128>), grid, block, 0, s, P, a); \
-        } else if constexpr (BT == DT_F32) {                                                         \
-            SPMM_WIN_NP(MB, 128);                                                                    \
-        } else {                                                                                     \
-            if (a.win_np == 128) SPMM_WIN_NP(MB, 128);                                               \
-            else if (a.win_np == 64) SPMM_WIN_NP(MB, 64);                                            \
-            else SPMM_WIN_NP(MB, 32);                                                                \
-        }                                                                                            \
-    } while (0)
-    switch (P.H) {
-    case 16: SPMM_WIN(1); break;
-    case 32: SPMM_WIN(2); break;
-    case 64: SPMM_WIN(4); break;
-    default: return hipErrorInvalidValue;
-    }
-#undef SPMM_WIN
-#undef SPMM_WIN_NP
-    return hipGetLastError();
+    const int64_t waves = (int64_t)(partial ? P.n_wpart : P.n_win) * a.win_panels * a.win_subs;
+    if (waves == 0) return hipSuccess;
+    return window_shape<BT>(P, a, [&](auto mb, auto mbw, auto cw, auto buf) {
+        launch_kernel((window_kernel<VT, BT, TT, decltype(mb)::value, decltype(mbw)::value, decltype(cw)::value,
+                                     decltype(buf)::value>),
+                      dim3(grid_for_waves(waves)), dim3(256), 0, s, P, a, partial ? 1 : 0);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_segment(const DevPlan &P, int32_t vt, int32_t bt, const RunArgs &a, hipStream_t s) {
@@ -224,8 +186,8 @@ hipError_t launch_vector(const DevPlan &P, int32_t vt, int32_t bt, const RunArgs
     return hipErrorInvalidValue;
 }
 
-static hipError_t window_any(const DevPlan &P, int32_t vt, int32_t bt, int32_t tt, const RunArgs &a,
-                             hipStream_t s, bool partial) {
+hipError_t launch_window(const DevPlan &P, int32_t vt, int32_t bt, int32_t tt, const RunArgs &a,
+                         hipStream_t s, bool partial) {
     if (vt == DT_F32 && bt == DT_F32 && tt == DT_BF16) return win_dispatch<DT_F32, DT_F32, DT_BF16>(P, a, s, partial);
     if (vt == DT_F32 && bt == DT_BF16 && tt == DT_BF16) return win_dispatch<DT_F32, DT_BF16, DT_BF16>(P, a, s, partial);
     if (vt == DT_BF16 && bt == DT_BF16 && tt == DT_BF16) return win_dispatch<DT_BF16, DT_BF16, DT_BF16>(P, a, s, partial);
@@ -233,18 +195,7 @@ static hipError_t window_any(const DevPlan &P, int32_t vt, int32_t bt, int32_t t
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_window(const DevPlan &P, int32_t vt, int32_t bt, int32_t tt, const RunArgs &a,
-                         hipStream_t s) {
-    return window_any(P, vt, bt, tt, a, s, false);
-}
-
-hipError_t launch_window_partial(const DevPlan &P, int32_t vt, int32_t bt, int32_t tt,
-                                 const RunArgs &a, hipStream_t s) {
-    return window_any(P, vt, bt, tt, a, s, true);
-}
-
-// E, CPL: chunks of the segment and vector kernels; EW, CW: of the windows'.
-template <int VT, int BT, int TT, int E, int CPL, int EW, int CW, int VAR>
+template <int VT, int BT, int TT, int E, int CPL, int VAR>
 static hipError_t batch_variant(const BatchHeader *hdr, const BatchEntry *tab, const BatchGrids &g,
                                 hipStream_t s, BatchGrids *occ) {
     if (occ) {
@@ -257,66 +208,61 @@ static hipError_t batch_variant(const BatchHeader *hdr, const BatchEntry *tab, c
         if (e != hipSuccess) return e;
         occ->vec = (unsigned)o;
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &o, batch_window_kernel<VT, BT, TT, EW, CW, false>, 256, 0);
+            &o, batch_window_kernel<VT, BT, TT, false>, 256, 0);
         occ->win = (unsigned)o;
         return e;
     }
     // phase 1: partial sums (segments, window tile chunks); phase 2: owners
     hipLaunchKernelGGL((batch_segment_kernel<VT, BT, E, CPL, VAR == 0>), dim3(g.seg), dim3(256), 0, s, hdr, tab);
-    hipLaunchKernelGGL((batch_window_kernel<VT, BT, TT, EW, CW, true>), dim3(g.win), dim3(256), 0, s,
+    hipLaunchKernelGGL((batch_window_kernel<VT, BT, TT, true>), dim3(g.win), dim3(256), 0, s,
                        hdr, tab);
     hipLaunchKernelGGL((batch_vector_kernel<VT, BT, E, CPL, VAR>), dim3(g.vec), dim3(256), 0, s, hdr, tab);
-    hipLaunchKernelGGL((batch_window_kernel<VT, BT, TT, EW, CW, false>), dim3(g.win), dim3(256), 0,
+    hipLaunchKernelGGL((batch_window_kernel<VT, BT, TT, false>), dim3(g.win), dim3(256), 0,
                        s, hdr, tab);
     return hipGetLastError();
 }
 
 template <int VT, int BT, int TT, int VAR>
 static hipError_t batch_types_var(const BatchHeader *hdr, const BatchEntry *tab, int vec_ok,
-                                  int win_vec, int cpl, const BatchGrids &g, hipStream_t s,
-                                  BatchGrids *occ) {
+                                  int cpl, const BatchGrids &g, hipStream_t s, BatchGrids *occ) {
     constexpr int EV = BT == DT_F32 ? 4 : 8;
-    if (!vec_ok) return batch_variant<VT, BT, TT, 1, 2, 1, 2, VAR>(hdr, tab, g, s, occ);
-    if (!win_vec) {
-        if (cpl == 1) return batch_variant<VT, BT, TT, EV, 1, 1, 2, VAR>(hdr, tab, g, s, occ);
-        return batch_variant<VT, BT, TT, EV, 2, 1, 2, VAR>(hdr, tab, g, s, occ);
-    }
-    if (cpl == 1) return batch_variant<VT, BT, TT, EV, 1, EV, 1, VAR>(hdr, tab, g, s, occ);
-    return batch_variant<VT, BT, TT, EV, 2, EV, 2, VAR>(hdr, tab, g, s, occ);
+    if (!vec_ok) return batch_variant<VT, BT, TT, 1, 2, VAR>(hdr, tab, g, s, occ);
+    if (cpl == 1) return batch_variant<VT, BT, TT, EV, 1, VAR>(hdr, tab, g, s, occ);
+    return batch_variant<VT, BT, TT, EV, 2, VAR>(hdr, tab, g, s, occ);
 }
 
 template <int VT, int BT, int TT>
-static hipError_t batch_types(const BatchHeader *hdr, const BatchEntry *tab, int vec_ok, int win_vec,
-                              int cpl, int var, const BatchGrids &g, hipStream_t s, BatchGrids *occ) {
-    if (var == 3) return batch_types_var<VT, BT, TT, 3>(hdr, tab, vec_ok, win_vec, cpl, g, s, occ);
-    if (var == 2) return batch_types_var<VT, BT, TT, 2>(hdr, tab, vec_ok, win_vec, cpl, g, s, occ);
-    if (var == 1) return batch_types_var<VT, BT, TT, 1>(hdr, tab, vec_ok, win_vec, cpl, g, s, occ);
-    return batch_types_var<VT, BT, TT, 0>(hdr, tab, vec_ok, win_vec, cpl, g, s, occ);
+static hipError_t batch_types(const BatchHeader *hdr, const BatchEntry *tab, int vec_ok, int cpl,
+                              int var, const BatchGrids &g, hipStream_t s, BatchGrids *occ) {
+    if (var == 3) return batch_types_var<VT, BT, TT, 3>(hdr, tab, vec_ok, cpl, g, s, occ);
+    if (var == 2) return batch_types_var<VT, BT, TT, 2>(hdr, tab, vec_ok, cpl, g, s, occ);
+    if (var == 1) return batch_types_var<VT, BT, TT, 1>(hdr, tab, vec_ok, cpl, g, s, occ);
+    return batch_types_var<VT, BT, TT, 0>(hdr, tab, vec_ok, cpl, g, s, occ);
 }
 
 static hipError_t batch_any(const BatchHeader *hdr, const BatchEntry *tab, int32_t vt, int32_t bt,
-                            int32_t tt, int vec_ok, int win_vec, int cpl, int var, const BatchGrids &g,
+                            int32_t tt, int vec_ok, int cpl, int var, const BatchGrids &g,
                             hipStream_t s, BatchGrids *occ) {
     if (vt == DT_F32 && bt == DT_F32 && tt == DT_BF16)
-        return batch_types<DT_F32, DT_F32, DT_BF16>(hdr, tab, vec_ok, win_vec, cpl, var, g, s, occ);
+        return batch_types<DT_F32, DT_F32, DT_BF16>(hdr, tab, vec_ok, cpl, var, g, s, occ);
     if (vt == DT_F32 && bt == DT_BF16 && tt == DT_BF16)
-        return batch_types<DT_F32, DT_BF16, DT_BF16>(hdr, tab, vec_ok, win_vec, cpl, var, g, s, occ);
+        return batch_types<DT_F32, DT_BF16, DT_BF16>(hdr, tab, vec_ok, cpl, var, g, s, occ);
     if (vt == DT_BF16 && bt == DT_BF16 && tt == DT_BF16)
-        return batch_types<DT_BF16, DT_BF16, DT_BF16>(hdr, tab, vec_ok, win_vec, cpl, var, g, s, occ);
+        return batch_types<DT_BF16, DT_BF16, DT_BF16>(hdr, tab, vec_ok, cpl, var, g, s, occ);
     if (vt == DT_F16 && bt == DT_F16 && tt == DT_F16)
-        return batch_types<DT_F16, DT_F16, DT_F16>(hdr, tab, vec_ok, win_vec, cpl, var, g, s, occ);
+        return batch_types<DT_F16, DT_F16, DT_F16>(hdr, tab, vec_ok, cpl, var, g, s, occ);
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_batch(const BatchHeader *hdr, const BatchEntry *tab, int32_t vt, int32_t bt,
-                        int32_t tt, int vec_ok, int win_vec, int cpl, int var, const BatchGrids &grids,
+                        int32_t tt, int vec_ok, int cpl, int var, const BatchGrids &grids,
                         hipStream_t s) {
-    return batch_any(hdr, tab, vt, bt, tt, vec_ok, win_vec, cpl, var, grids, s, nullptr);
+    return batch_any(hdr, tab, vt, bt, tt, vec_ok, cpl, var, grids, s, nullptr);
 }
 
-hipError_t batch_occupancy(int32_t vt, int32_t bt, int32_t tt, int vec_ok, int win_vec, int cpl, int var,
+hipError_t batch_occupancy(int32_t vt, int32_t bt, int32_t tt, int vec_ok, int cpl, int var,
                            BatchGrids *per_cu) {
-    return batch_any(nullptr, nullptr, vt, bt, tt, vec_ok, win_vec, cpl, var, BatchGrids{}, nullptr, per_cu);
+    return batch_any(nullptr, nullptr, vt, bt, tt, vec_ok, cpl, var, BatchGrids{}, nullptr, per_cu);
 }
 
 hipError_t launch_copy(const float4 *src, float4 *dst, int64_t n4, hipStream_t s) {

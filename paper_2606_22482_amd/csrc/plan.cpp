@@ -835,12 +835,14 @@ void derive_exec_tables(HostPlan &P) {
     P.win_nsseg.assign(W, 0);
     P.win_row_sid.assign(W * H, -1);
     P.n_dep = 0;
+    P.win_rem = 0;
     if (W == 0) return;
     P.seg_win.assign(P.seg_row.size(), -1);
     for (int64_t w = 0; w < W; ++w) {
         int32_t ns = 0;
         for (int64_t s = 0; s < H; ++s) {
             const int32_t r = P.windows[w * H + s];
+            if (r >= 0 && P.nseg[r] == 0) P.win_rem += P.rem_ptr[r + 1] - P.rem_ptr[r];
             if (r < 0 || P.nseg[r] == 0) continue;
             P.win_row_sid[w * H + s] = P.win_seg[w] + ns;
             ns += P.nseg[r];

@@ -65,6 +65,7 @@ struct HostPlan {
     std::vector<int32_t> win_nsseg;     // [W] segments of the window's split rows
     std::vector<int32_t> win_row_sid;   // [W*H] first segment of a window row that is split, else -1
     int32_t n_dep = 0;                  // windows with a slot
+    int64_t win_rem = 0;                // remainder entries of window rows that are not split
 
     // ---- device-facing copies of the remainder ----
     std::vector<int32_t> rem_ptr32;     // [m+1]

@@ -77,18 +77,29 @@ namespace {
 // Every sub-array is followed by at least 16 zero bytes, so a kernel that
 // clamps an index into [0, size] (an empty range included) stays inside the
 // allocation; the window kernel issues its predicated loads that way.
+// Parts from host memory first (one copy brings them), then those whose source
+// is device memory; 16 bytes of zeros (`pad`) or more behind each.
 struct Arena {
     std::vector<std::pair<const void *, size_t>> parts;
-    std::vector<size_t> offs;
+    std::vector<size_t> offs, pads;
     std::vector<uint8_t> on_device;  // the part's source is device memory
-    size_t total = 0;
-    size_t add(const void *p, size_t bytes, bool dev = false) {
-        total = (total + 255) & ~size_t(255);
-        offs.push_back(total);
+    size_t host = 0, total = 0;
+    size_t add(const void *p, size_t bytes, bool dev = false, size_t pad = 16) {
         parts.push_back({p, bytes});
         on_device.push_back(dev ? 1 : 0);
-        total += bytes + 16;
+        pads.push_back(pad);
         return parts.size() - 1;
+    }
+    void layout() {
+        offs.resize(parts.size());
+        for (int dev = 0; dev < 2; ++dev) {
+            for (size_t i = 0; i < parts.size(); ++i) {
+                if (on_device[i] != dev) continue;
+                offs[i] = total;
+                total += (parts[i].second + pads[i] + 255) & ~size_t(255);
+            }
+            if (!dev) host = total;
+        }
     }
 };
 
@@ -159,7 +170,6 @@ spmm_status upload_plan(spmm_plan_t *p, const DeviceArrays *da) {
         HostPlan &h = p->hp;
         Arena a;
         std::vector<int32_t> win_tile_ptr32(h.win_tile_ptr.begin(), h.win_tile_ptr.end());
-        std::vector<int32_t> tile_val_ptr32(h.tile_val_ptr.begin(), h.tile_val_ptr.end());
         const size_t i_rem_ptr = add_vec(a, h.rem_ptr32);
         const size_t i_rem_col = da ? a.add(da->rem_col, 4 * da->nrem, true) : add_vec(a, h.rem_col);
         const size_t i_rem_val = da ? a.add(da->rem_val, da->nrem * (size_t)dtype_size(h.val_type), true)
@@ -198,10 +208,14 @@ spmm_status upload_plan(spmm_plan_t *p, const DeviceArrays *da) {
         const size_t i_seg_order = add_vec(a, seg_order);
         const size_t nt = h.tile_window.size();
         const size_t i_tile_cols = da ? a.add(da->tile_cols, 4 * nt * h.opts.kt, true) : add_vec(a, h.tile_cols);
-        const size_t i_tile_bitmap =
-            da ? a.add(da->tile_bitmap, 4 * nt * h.opts.window_h, true) : add_vec(a, h.tile_bitmap);
-        const size_t i_tile_val_ptr = add_vec(a, tile_val_ptr32);
-        const size_t i_tile_vals = da ? a.add(da->tile_vals, 2 * da->nvals, true) : add_vec(a, h.tile_vals);
+        // The tiles' 16-bit values, dense: an MFMA operand is then one aligned
+        // load.  A plan's tiles hold at least alpha of their slots (1/16 by
+        // default), and a dense tile row is 64 bytes beside the 32 B rows that
+        // the tile gathers.
+        // A tile of zeros follows them (odd numbers of tiles are padded with it).
+        const size_t slots = nt * (size_t)h.opts.window_h * h.opts.kt, pad = (size_t)h.opts.window_h * h.opts.kt;
+        const size_t i_tile_dense = a.add(da ? da->tile_dense : nullptr, 2 * slots, da != nullptr, 2 * pad);
+        const size_t i_tile_bitmap = a.add(da ? da->tile_bitmap : nullptr, da ? 4 * nt * h.opts.window_h : 0, true);
         const size_t i_win_part = add_vec(a, h.win_part);
         const size_t i_wpart_win = add_vec(a, h.wpart_win);
         const size_t i_wpart_t0 = add_vec(a, h.wpart_t0);
@@ -213,19 +227,28 @@ spmm_status upload_plan(spmm_plan_t *p, const DeviceArrays *da) {
         const size_t i_win_row_sid = add_vec(a, h.win_row_sid);
         static const uint8_t kZeros[256] = {};
         const size_t i_zeros = a.add(kZeros, sizeof(kZeros));
-        const size_t total = std::max<size_t>(a.total, 256);
+        a.layout();
+        const size_t total = a.total;
 
-        std::vector<uint8_t> image(total, 0);
+        std::vector<uint8_t> image(a.host, 0);
         for (size_t i = 0; i < a.parts.size(); ++i)
-            if (a.parts[i].second && !a.on_device[i])
+            if (a.parts[i].second && !a.on_device[i] && a.parts[i].first)
                 std::memcpy(image.data() + a.offs[i], a.parts[i].first, a.parts[i].second);
+
+        if (!da) {
+            uint16_t *dense = reinterpret_cast<uint16_t *>(image.data() + a.offs[i_tile_dense]);
+            size_t v = 0;
+            for (size_t i = 0; i < h.tile_bitmap.size(); ++i)  // row-major over set bits
+                for (uint32_t w = h.tile_bitmap[i]; w; w &= w - 1) dense[i * 32 + __builtin_ctz(w)] = h.tile_vals[v++];
+        }
 
         int dev = 0;
         SPMM_TRY_HIP(hipGetDevice(&dev), "hipGetDevice");
         void *d = nullptr;
         hipError_t e = hipMalloc(&d, total);
         if (e != hipSuccess) return set_error(SPMM_ERR_OOM, std::string("hipMalloc(plan): ") + hipGetErrorString(e));
-        e = hipMemcpy(d, image.data(), total, hipMemcpyHostToDevice);
+        e = hipMemcpy(d, image.data(), a.host, hipMemcpyHostToDevice);
+        if (e == hipSuccess && total > a.host) e = hipMemsetAsync(static_cast<uint8_t *>(d) + a.host, 0, total - a.host, 0);
         for (size_t i = 0; i < a.parts.size() && e == hipSuccess; ++i)
             if (a.parts[i].second && a.on_device[i])
                 e = hipMemcpy(static_cast<uint8_t *>(d) + a.offs[i], a.parts[i].first, a.parts[i].second,
@@ -261,9 +284,9 @@ spmm_status upload_plan(spmm_plan_t *p, const DeviceArrays *da) {
         for (size_t w = 0; w < h.win_order.size() && order_id; ++w) order_id = h.win_order[w] == (int32_t)w;
         dp.win_order = order_id ? nullptr : reinterpret_cast<const int32_t *>(at(i_win_order));
         dp.tile_cols = reinterpret_cast<const int32_t *>(at(i_tile_cols));
-        dp.tile_bitmap = reinterpret_cast<const uint32_t *>(at(i_tile_bitmap));
-        dp.tile_val_ptr = reinterpret_cast<const int32_t *>(at(i_tile_val_ptr));
-        dp.tile_vals = reinterpret_cast<const uint16_t *>(at(i_tile_vals));
+        dp.tile_dense = reinterpret_cast<const uint16_t *>(at(i_tile_dense));
+        dp.n_tiles = (int32_t)nt;
+        dp.tile_bitmap = da ? reinterpret_cast<const uint32_t *>(at(i_tile_bitmap)) : nullptr;
         dp.n_wpart = (int32_t)h.wpart_win.size();
         dp.win_tmax = h.win_tiles;
         dp.win_part = reinterpret_cast<const int32_t *>(at(i_win_part));
@@ -388,7 +411,11 @@ spmm_status ensure_host_remainder(spmm_plan_t *p) {
         SPMM_TRY_HIP(d2h(h.rem_val.data(), p->dp.rem_val, sval * nrem), "hipMemcpy(plan)");
         SPMM_TRY_HIP(d2h(h.tile_cols.data(), p->dp.tile_cols, 4 * h.tile_cols.size()), "hipMemcpy(plan)");
         SPMM_TRY_HIP(d2h(h.tile_bitmap.data(), p->dp.tile_bitmap, 4 * h.tile_bitmap.size()), "hipMemcpy(plan)");
-        SPMM_TRY_HIP(d2h(h.tile_vals.data(), p->dp.tile_vals, 2 * nv), "hipMemcpy(plan)");
+        std::vector<uint16_t> dense(nt * h.opts.window_h * h.opts.kt);
+        SPMM_TRY_HIP(d2h(dense.data(), p->dp.tile_dense, 2 * dense.size()), "hipMemcpy(plan)");
+        size_t v = 0;
+        for (size_t i = 0; i < h.tile_bitmap.size(); ++i)
+            for (uint32_t w = h.tile_bitmap[i]; w && v < nv; w &= w - 1) h.tile_vals[v++] = dense[i * 32 + __builtin_ctz(w)];
         SPMM_TRY_HIP(d2h(rs.data(), p->aux, 4 * nrem), "hipMemcpy(plan)");
         SPMM_TRY_HIP(d2h(ts.data(), static_cast<const int32_t *>(p->aux) + nrem, 4 * nv), "hipMemcpy(plan)");
         h.rem_src.assign(rs.begin(), rs.end());
@@ -593,7 +620,6 @@ spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void
     // One element a lane remains for rows below one chunk only: on a graph of
     // 200,003 rows (2.8M entries, f32) at N = 47 it took 229 us, chunks 95 us.
     a.vec_ok = N >= E && (uintptr_t)B % sb == 0 && (uintptr_t)C % 4 == 0;
-    a.win_vec = N % E == 0 && ldb % E == 0 && ldc % 4 == 0 && (uintptr_t)B % 16 == 0 && (uintptr_t)C % 16 == 0;
     int np = h.opts.n_panel > 0 ? std::min(h.opts.n_panel, N) : N;
     const int maxnp = a.vec_ok ? 128 * E : 128;
     np = std::min(np, maxnp);
@@ -609,24 +635,43 @@ spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void
     // leading dimension are not
     const bool al4 = sb == 4 || (N % 2 == 0 && ldb % 2 == 0 && (uintptr_t)B % 4 == 0);
     a.cold_aux = (b_span < 4294967295.0 && al4 && h.opts.cold_policy != 0) ? h.opts.cold_policy : -1;
-    a.b_rec = b_span < 4294967040.0 && al4 ? (uint32_t)b_span : 0u;
+    // (a row of -1 has to wrap to an offset beyond the resource as well)
+    a.b_rec = b_span + (double)ldb * sb < 4294967040.0 && al4 ? (uint32_t)b_span : 0u;
     // f32 rows of more than 32 columns that are not whole chunks: size classes
     // sum every row as the packed-row variant does (one order for both at such
     // widths), and that variant is the faster one for f32 B
     a.pipeline = h.opts.pipeline == 3 && sb == 4 && N % E != 0 && N > 32 ? 2 : h.opts.pipeline;
-    // narrow 16-bit B: windows stage panels of 64 or 32 columns, so that no
-    // staged column and no MFMA block is padding
-    int wnp = 128;
-    if (a.win_vec && sb == 2) wnp = N <= 32 ? 32 : N <= 64 ? 64 : 128;
-    set_window_panels(a, N, E, wnp);
+    // Window panels: 16 lanes of up to 16 bytes of a B row each (128 columns
+    // of 16-bit B, 64 of f32), narrower for narrower N (a lane's chunk has to
+    // fit in a row).  A wave takes all 64 rows of a high window, so that a B
+    // row is loaded once for them; where that leaves the chip too few waves,
+    // the panels are halved to 64 columns, then the rows split over 2 and 4
+    // waves, then the panels halved again.  Plans with partial items want more
+    // waves, which share the combining of the parts.  Measured (attention
+    // masks, us, 1 / 2 / 4 waves a window in panels of 128, then of 64):
+    // 32,768 rows, N = 256 (1024 waves of 128 columns): 117 / 159 / 227, 151 / 209 / 328;
+    // 24,000, N = 177 (750): 108 / 167 / 215, 143 / 162 / 218;
+    // 20,000, N = 128 (939, partial items): 78 / 75 / 97, 64 / 85 / 113;
+    // 3,001, N = 128 (94, partial items): 43 / 25 / 19, 27 / 18 / 13, of 32: 19 / 13 / 12.
+    // Short windows keep the matrix units less busy than the loads around them
+    // and take two waves at once (100,000 rows in blocks, N = 128, 13 tiles a
+    // window: 59 / 50 / 62).  Where a window gathers more B rows for its
+    // remainders than for its tiles, panels of 64 columns, which hold twice the
+    // entries in flight a row (graph of 500,000 rows, 90 entries a row beside
+    // the tiles, N = 128 of bf16: MFMA path 206 us in panels of 128, 142 of 64).
+    a.win_np = N == 1 ? 16 : N <= 32 ? 32 : N <= 64 || sb == 4 ? 64 : 128;
+    const int mb = h.opts.window_h / 16;
+    const int64_t items = (int64_t)p->dp.n_win + p->dp.n_wpart;
+    const int64_t want = p->dp.n_wpart > 0 ? 1100 : 700;
+    auto waves = [&] { return items * ((N + a.win_np - 1) / a.win_np) * a.win_subs; };
+    // (one block a wave where the kernels take no more: see window_shape)
+    a.win_subs = mb == 4 && N > 1 && h.opts.exec != 3 && (a.b_rec != 0 || sb == 2) ? 1 : mb;
+    if (a.win_np == 128 && (waves() < want || h.win_rem > (int64_t)p->dp.n_tiles * h.opts.kt)) a.win_np = 64;
+    if (a.win_subs < mb && p->dp.n_tiles < 32 * items) a.win_subs = 2;
+    while (a.win_subs < mb && waves() < want) a.win_subs *= 2;
+    if (a.win_np == 64 && N > 32 && waves() < (mb == 1 ? 1600 : want)) a.win_np = 32;
+    a.win_panels = (N + a.win_np - 1) / a.win_np;
     return SPMM_OK;
-}
-
-void set_window_panels(RunArgs &a, int N, int E, int np) {
-    a.win_np = np;
-    a.win_panels = (N + np - 1) / np;
-    const int wchunks = a.win_vec ? np / E : np;
-    a.win_lpr_log2 = ilog2_ceil(std::min(wchunks, 64));
 }
 }  // namespace spmm
 
@@ -719,21 +764,21 @@ void coschedule_layout(const spmm_plan_t *p, RunArgs &a) {
     auto up8 = [](int64_t x) { return (int32_t)((x + 7) & ~int64_t(7)); };
     a.seg_blocks = up8(((int64_t)P.n_seg * a.n_panels + 3) / 4);
     a.vec_blocks = (int32_t)(((int64_t)P.n_vitems * a.n_panels + 3) / 4);
-    a.wpart_blocks = up8((int64_t)P.n_wpart * a.win_panels);
-    a.win_blocks = (int32_t)((int64_t)P.n_win * a.win_panels);
+    a.wpart_blocks = up8(((int64_t)P.n_wpart * a.win_panels * a.win_subs + 3) / 4);
+    a.win_blocks = (int32_t)(((int64_t)P.n_win * a.win_panels * a.win_subs + 3) / 4);
 }
 
 // The two grids of a co-scheduled run go to two streams only when each has
-// at least a workgroup per CU (256); otherwise one of them is too small to
+// at least a workgroup or a window item per CU (256); otherwise one of them is too small to
 // pay for the fork and join (measured about 25-30 us on gfx950) and both run
 // on the run's stream, the MFMA path first.
 bool fork_paths(const RunArgs &a) {
-    return a.seg_blocks + a.vec_blocks >= 256 && a.wpart_blocks + a.win_blocks >= 256;
+    return a.seg_blocks + a.vec_blocks >= 256 && (a.wpart_blocks + a.win_blocks) * 4 >= 256 * a.win_subs;
 }
 
 size_t counter_ints(const spmm_plan_t *p, const RunArgs &a) {
     if (serial_exec(p, a)) return 0;
-    return (size_t)a.n_panels * p->dp.n_seg + (size_t)a.win_panels * p->dp.n_dep;
+    return (size_t)a.n_panels * p->dp.n_seg + (size_t)a.win_panels * p->dp.n_dep * a.win_subs;
 }
 
 spmm_status launch_plan(const spmm_plan_t *p, const RunArgs &a0, hipStream_t s, spmm_timer_t *t,
@@ -775,7 +820,7 @@ spmm_status launch_plan(const spmm_plan_t *p, const RunArgs &a0, hipStream_t s, 
         }
         if (P.n_wpart > 0) {
             st = timed(SPMM_KERNEL_WINDOW_PARTIAL, s,
-                       [&] { return launch_window_partial(P, h.val_type, h.b_type, h.tile_type, a, s); });
+                       [&] { return launch_window(P, h.val_type, h.b_type, h.tile_type, a, s, true); });
             if (st != SPMM_OK) return st;
         }
         if (P.n_vitems > 0) {
@@ -784,7 +829,7 @@ spmm_status launch_plan(const spmm_plan_t *p, const RunArgs &a0, hipStream_t s, 
         }
         if (P.n_win > 0) {
             st = timed(SPMM_KERNEL_WINDOW, s,
-                       [&] { return launch_window(P, h.val_type, h.b_type, h.tile_type, a, s); });
+                       [&] { return launch_window(P, h.val_type, h.b_type, h.tile_type, a, s, false); });
             if (st != SPMM_OK) return st;
         }
         return SPMM_OK;
@@ -801,7 +846,7 @@ spmm_status launch_plan(const spmm_plan_t *p, const RunArgs &a0, hipStream_t s, 
         // holds fewer scalar registers and ran 0.168 against 0.178 ms on the
         // block-community matrix)
         return timed(SPMM_KERNEL_WINDOW, s,
-                     [&] { return launch_window(P, h.val_type, h.b_type, h.tile_type, a, s); });
+                     [&] { return launch_window(P, h.val_type, h.b_type, h.tile_type, a, s, false); });
     }
     if (h.opts.exec == 3 && mfma && vec && one_grid_supported(h.b_type, a))
         return timed(SPMM_KERNEL_ONE_GRID, s,

@@ -35,8 +35,8 @@ namespace spmm {
 struct DeviceArrays {
     const void *rem_col = nullptr, *rem_val = nullptr;     // [nrem]
     const void *tile_cols = nullptr, *tile_bitmap = nullptr;  // [T * kt], [T * H]
-    const void *tile_vals = nullptr;                        // [nvals]
-    size_t nrem = 0, nvals = 0;
+    const void *tile_dense = nullptr;                       // [T * H * kt]
+    size_t nrem = 0;
     std::vector<int32_t> seg_order;  // launch order of the segments (empty: id order)
 };
 spmm_status upload_plan(spmm_plan_t *p, const DeviceArrays *da);
@@ -74,8 +74,6 @@ bool fork_paths(const RunArgs &a);
 size_t counter_ints(const spmm_plan_t *p, const RunArgs &a);
 spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void *C, int64_t ldc,
                           RunArgs &a);
-// Window panels of np columns (128, 64 or 32) for a run with N columns.
-void set_window_panels(RunArgs &a, int N, int E, int np);
 spmm_status check_run(const spmm_plan_t *p, const void *B, int64_t ldb, void *C, int64_t ldc);
 spmm_status launch_plan(const spmm_plan_t *p, const RunArgs &a, hipStream_t s, spmm_timer_t *t,
                         const RunContext &ctx);

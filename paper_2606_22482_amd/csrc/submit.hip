@@ -129,14 +129,13 @@ extern "C" spmm_status spmm_submit(const spmm_work *items, int32_t count, void *
         const spmm_plan_t *p = items[i].plan;
         if (p->hp.m == 0) continue;
         make_run_args(p, items[i].B, items[i].ldb, items[i].C, items[i].ldc, args[i]);
-        // the batched window kernels stage 128-column panels
-        set_window_panels(args[i], (int)p->hp.n, chunk_elems(p->hp.b_type), 128);
+        args[i].win_subs = p->hp.opts.window_h / 16;  // the batched window kernels' waves take one 16-row block
         ws_floats += workspace_floats(p->hp, true);
         const int E = args[i].vec_ok ? chunk_elems(p->hp.b_type) : 1;
         const int chunks = (args[i].np + E - 1) / E;
         const int cpl = chunks > 64 ? 2 : 1;
         const uint64_t key = (uint64_t)p->hp.val_type | ((uint64_t)p->hp.b_type << 4) |
-                             ((uint64_t)p->hp.tile_type << 8) | ((uint64_t)args[i].vec_ok << 12) | ((uint64_t)args[i].win_vec << 13) |
+                             ((uint64_t)p->hp.tile_type << 8) | ((uint64_t)args[i].vec_ok << 12) |
                              ((uint64_t)cpl << 16) | ((uint64_t)args[i].pipeline << 20);
         groups[key].push_back(i);
     }
@@ -164,7 +163,7 @@ extern "C" spmm_status spmm_submit(const spmm_work *items, int32_t count, void *
         const uint64_t key = kv.first;
         const std::vector<int32_t> &idx = kv.second;
         const int32_t vt = key & 0xF, bt = (key >> 4) & 0xF, tt = (key >> 8) & 0xF;
-        const int vec_ok = (key >> 12) & 1, win_vec = (key >> 13) & 1, cpl = (key >> 16) & 0xF, var = (key >> 20) & 0xF;
+        const int vec_ok = (key >> 12) & 0xF, cpl = (key >> 16) & 0xF, var = (key >> 20) & 0xF;
         // Work of each matrix (~ entries * N plus rows * N).  Whole matrices go
         // to the 8 XCDs by longest processing time, so that each XCD's L2
         // serves one matrix's B at a time.  While that leaves an XCD above 120%
@@ -215,8 +214,8 @@ extern "C" spmm_status spmm_submit(const spmm_work *items, int32_t count, void *
                 const RunArgs &a = args[idx[j]];
                 const int64_t n4[4] = {(int64_t)p->dp.n_seg * a.n_panels,
                                        (int64_t)p->dp.n_vitems * a.n_panels,
-                                       (int64_t)p->dp.n_win * a.win_panels,
-                                       (int64_t)p->dp.n_wpart * a.win_panels};
+                                       (int64_t)p->dp.n_win * a.win_panels * a.win_subs,
+                                       (int64_t)p->dp.n_wpart * a.win_panels * a.win_subs};
                 Ent e{j, {0, 0, 0, 0}, {0, 0, 0, 0}};
                 if (!split[j]) {
                     if (xcd_of[j] != x) continue;
@@ -310,7 +309,7 @@ extern "C" spmm_status spmm_submit(const spmm_work *items, int32_t count, void *
         }
         if (!vg.exec) {
             BatchGrids occ;
-            SPMM_TRY_HIP(batch_occupancy(vt, bt, tt, vec_ok, win_vec, cpl, var, &occ), "occupancy");
+            SPMM_TRY_HIP(batch_occupancy(vt, bt, tt, vec_ok, cpl, var, &occ), "occupancy");
             // each kernel's grid is its resident workgroups per CU times the CUs,
             // in a multiple of 8 so that every XCD gets the same number; the
             // segment kernel takes at most 3 per CU, its fastest measured grid
@@ -327,7 +326,7 @@ extern "C" spmm_status spmm_submit(const spmm_work *items, int32_t count, void *
             const auto *dh = static_cast<const BatchHeader *>(vg.dtab);
             const auto *dt = reinterpret_cast<const BatchEntry *>(static_cast<uint8_t *>(vg.dtab) + kHeaderBytes);
             SPMM_TRY_HIP(hipStreamBeginCapture(ctx.capture, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-            hipError_t le = launch_batch(dh, dt, vt, bt, tt, vec_ok, win_vec, cpl, var, vg.grids, ctx.capture);
+            hipError_t le = launch_batch(dh, dt, vt, bt, tt, vec_ok, cpl, var, vg.grids, ctx.capture);
             hipGraph_t graph = nullptr;
             hipError_t ce = hipStreamEndCapture(ctx.capture, &graph);
             if (le != hipSuccess) return hip_error(le, "batched launch (capture)");
