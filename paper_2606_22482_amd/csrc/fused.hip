@@ -58,7 +58,7 @@ __device__ __forceinline__ void mfma_path(const DevPlan &P, const RunArgs &a, in
 }
 
 template <int VT, int BT, int E, int CPL, int VAR>
-__global__ __launch_bounds__(256) void vector_path_kernel(DevPlan P, RunArgs a) {
+__global__ __launch_bounds__(256, (vector_waves<BT, CPL, VAR>())) void vector_path_kernel(DevPlan P, RunArgs a) {
     vector_path<VT, BT, E, CPL, VAR>(P, a, blockIdx.x);
 }
 

@@ -438,47 +438,129 @@ __device__ __forceinline__ void chunk_layout(int ncol0, int ncols, const Lanes &
     }
 }
 
+// Entries of a row (or segment) held by the lanes that sum it: a block of
+// `groups` lane groups, whose lane l of `span` holds entries l and span + l of
+// those from the hold's first on (at clamped indices: a real entry of the row).
+// Two coalesced loads of each array serve as many steps as the hold spans,
+// where every lane loading its own group's entries takes 2 U loads a step, each
+// of one entry per group.  The vector path is bound by gathers in flight, and
+// the entry loads took half of its load slots (graphs, us, own loads / held:
+// 2^20 rows, N = 128 of f32 973 / 900; 500,000, N = 256 of bf16 568 / 492;
+// 200,003, N = 47 of f32 105 / 95; 64 uneven f16 matrices in a batch
+// 1192 / 1015).  Also loading the next hold or the next rows' entries ahead
+// costs registers and gained nothing (2^20 rows: 934 and 1052 us).
+struct Hold {
+    int c[2];
+    float v[2];
+};
+template <int VT>
+__device__ __forceinline__ void load_hold(const int32_t *__restrict__ rcol, const void *__restrict__ rval, int p,
+                                          int p1, int l, int span, Hold &h) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int q = max(min(p + k * span + l, p1 - 1), 0);
+        h.c[k] = __builtin_nontemporal_load(rcol + q);
+        h.v[k] = load_val<VT>(rval, q);
+    }
+}
+
 // acc += sum over entries [p0, p1) of v_p * B[col_p][panel columns], entry
-// p0 + i taken by group i % G in increasing i (see the file comment).
-template <int VT, int BT, int E, int CPL, int U, bool POL = false>
+// p0 + i taken by group i mod L.groups of the block, in increasing i (see the
+// file comment); `local` is this lane's group in the block, which starts at
+// lane `first`.
+template <int VT, int BT, int E, int CPL, int U, bool POL = false, bool HOLD = true>
+__device__ __forceinline__ void accumulate(const int32_t *__restrict__ rcol, const void *__restrict__ rval, int p0,
+                                           int p1, const void *__restrict__ B, int64_t ldb, uint32_t brec,
+                                           const bool (&cok)[CPL], const int64_t (&coff)[CPL], const Lanes &L,
+                                           int first, int local, int cold_aux, float (&acc)[CPL][E]) {
+    const __amdgpu_buffer_rsrc_t rs = b_resource(B, brec);
+    const int S = L.groups, step = S * U;
+    // Narrow rows load their own entries: a hold of theirs is no longer than a
+    // step, or (f32, fewer than 16 lanes a row) the hand-out costs more than
+    // the loads (20,000 rows, N = 32: 16.2 us, held 18.6).
+    if (!HOLD || (BT == DT_F32 ? L.lpr < 2 * U : 2 * L.lpr < U)) {
+        for (int p = p0 + local; p < p1; p += step) {
+            int col[U];
+            float v[U];
+            load_entries<VT, U, BT != DT_F32>(rcol, rval, p, p1, L, col, v);
+            gather_fma<BT, E, CPL, U, POL>(col, v, p, p1, B, rs, ldb, brec, cok, coff, L, cold_aux, acc);
+        }
+        return;
+    }
+    const int span = S * L.lpr, l = (int)(threadIdx.x & 63) - first;
+    for (int pb = p0; pb < p1; pb += 2 * span) {
+        Hold h;
+        load_hold<VT>(rcol, rval, pb, p1, l, span, h);
+        for (int t = 0; t < 2 * L.lpr && pb + t * S < p1; t += U) {
+            const int p = pb + t * S + local;
+            auto from = [&](int u, int lo, int hi) {  // entry u of this group
+                const int src = (first + ((t + u) & (L.lpr - 1)) * S + local) << 2;
+                return __builtin_amdgcn_ds_bpermute(src, t + u >= L.lpr ? hi : lo);
+            };
+            int col[U];
+            float v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) col[u] = from(u, h.c[0], h.c[1]);
+            if constexpr (BT == DT_F32 || POL) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    v[u] = __int_as_float(from(u, __float_as_int(h.v[0]), __float_as_int(h.v[1])));
+                gather_fma<BT, E, CPL, U, POL>(col, v, p, p1, B, rs, ldb, brec, cok, coff, L, cold_aux, acc);
+            } else {
+                // 16-bit rows: the values behind the gathers, in the columns'
+                // registers (batched kernel 104 -> 90)
+                Raw<BT, E> b[U][CPL];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c) {
+                        const int64_t boff = (int64_t)(col[u] & 0x7FFFFFFF) * ldb + coff[c];
+                        const bool ok = p + u * S < p1 && cok[c];
+                        if (brec != 0) load_raw_buf<BT, E>(rs, ok ? (uint32_t)(boff * 2) : brec, b[u][c]);
+                        else load_raw<BT, E, false>(B, boff, b[u][c]);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    v[u] = __int_as_float(from(u, __float_as_int(h.v[0]), __float_as_int(h.v[1])));
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (p + u * S < p1) {
+#pragma unroll
+                        for (int c = 0; c < CPL; ++c) fma_raw<BT, E>(v[u], b[u][c], acc[c]);
+                    }
+            }
+        }
+    }
+}
+
+// The same for one row on the whole wavefront.
+template <int VT, int BT, int E, int CPL, int U, bool POL = false, bool HOLD = true>
 __device__ __forceinline__ void seg_accumulate(const int32_t *__restrict__ rcol,
                                                const void *__restrict__ rval, int p0, int p1,
                                                const void *__restrict__ B, int64_t ldb, uint32_t brec,
                                                int ncol0, int ncols, const Lanes &L, int cold_aux,
                                                float (&acc)[CPL][E]) {
-    const __amdgpu_buffer_rsrc_t rs = b_resource(B, brec);
     bool cok[CPL];
     int64_t coff[CPL];
     chunk_layout<E, CPL>(ncol0, ncols, L, cok, coff);
-    const int step = L.groups * U;
-    for (int p = p0 + L.group; p < p1; p += step) {
-        int col[U];
-        float v[U];
-        load_entries<VT, U, BT != DT_F32>(rcol, rval, p, p1, L, col, v);
-        gather_fma<BT, E, CPL, U, POL>(col, v, p, p1, B, rs, ldb, brec, cok, coff, L, cold_aux, acc);
-    }
+    accumulate<VT, BT, E, CPL, U, POL, HOLD>(rcol, rval, p0, p1, B, ldb, brec, cok, coff, L, 0, L.group, cold_aux, acc);
 }
 
 // acc += sum over entries [p0, p1) of one row, all taken by this lane's group
 // in increasing order (each group works on its own row).
-template <int VT, int BT, int E, int CPL, int U, bool POL = false>
+template <int VT, int BT, int E, int CPL, int U, bool POL = false, bool HOLD = true>
 __device__ __forceinline__ void row_accumulate_group(const int32_t *__restrict__ rcol,
                                                      const void *__restrict__ rval, int p0, int p1,
                                                      const void *__restrict__ B, int64_t ldb,
                                                      uint32_t brec, int ncol0, int ncols,
                                                      const Lanes &L, int cold_aux,
                                                      float (&acc)[CPL][E]) {
-    const __amdgpu_buffer_rsrc_t rs = b_resource(B, brec);
     bool cok[CPL];
     int64_t coff[CPL];
     chunk_layout<E, CPL>(ncol0, ncols, L, cok, coff);
-    const Lanes one = L.single();
-    for (int p = p0; p < p1; p += U) {
-        int col[U];
-        float v[U];
-        load_entries<VT, U, BT != DT_F32>(rcol, rval, p, p1, one, col, v);
-        gather_fma<BT, E, CPL, U, POL>(col, v, p, p1, B, rs, ldb, brec, cok, coff, one, cold_aux, acc);
-    }
+    accumulate<VT, BT, E, CPL, U, POL, HOLD>(rcol, rval, p0, p1, B, ldb, brec, cok, coff, L.single(), L.group * L.lpr, 0,
+                                       cold_aux, acc);
 }
 
 template <int E, int CPL>
@@ -916,7 +998,7 @@ __device__ __forceinline__ int wave_inclusive_scan(int x) {
 // UL: entries per group and step; the short-row bound stays 2 unroll_of, so
 // the summation order (which depends only on a row's length) is the same for
 // any UL.
-template <int VT, int BT, int E, int CPL, bool FUSED = false, int UL = unroll_of<E, CPL>()>
+template <int VT, int BT, int E, int CPL, bool FUSED = false, int UL = unroll_of<E, CPL>(), bool HOLD = true>
 __device__ __forceinline__ void vector_item_packed(const DevPlan &P, const RunArgs &a, int wid) {
     constexpr int U = UL;
     constexpr int SHORT = 2 * unroll_of<E, CPL>();
@@ -953,7 +1035,7 @@ __device__ __forceinline__ void vector_item_packed(const DevPlan &P, const RunAr
 #pragma unroll
                     for (int x = 0; x < E; ++x) acc[c][x] = 0.0f;
                 if (L.group < k) {
-                    row_accumulate_group<VT, BT, E, CPL, U>(P.rem_col, P.rem_val, b, e, a.B, a.ldb, a.b_rec,
+                    row_accumulate_group<VT, BT, E, CPL, U, false, HOLD>(P.rem_col, P.rem_val, b, e, a.B, a.ldb, a.b_rec,
                                                             ncol0, ncols, L, a.cold_aux, acc);
 #pragma unroll
                     for (int c = 0; c < CPL; ++c) {
@@ -974,7 +1056,7 @@ __device__ __forceinline__ void vector_item_packed(const DevPlan &P, const RunAr
 #pragma unroll
                 for (int x = 0; x < E; ++x) acc[c][x] = 0.0f;
             if (e - b <= P.seg_len) {
-                seg_accumulate<VT, BT, E, CPL, U>(P.rem_col, P.rem_val, b, e, a.B, a.ldb, a.b_rec, ncol0, ncols,
+                seg_accumulate<VT, BT, E, CPL, U, false, HOLD>(P.rem_col, P.rem_val, b, e, a.B, a.ldb, a.b_rec, ncol0, ncols,
                                                   L, a.cold_aux, acc);
                 group_reduce<E, CPL>(acc, L);
             } else {
@@ -1101,12 +1183,20 @@ __device__ __forceinline__ void vector_item_classed(const DevPlan &P, const RunA
             sum_partials<E, CPL>(a.work, a.work_ld, my_sid, my_ns, ncol0, ncols, L, acc);
         Lanes Ls = L;
         Ls.groups = my_s;
-        for (int p = my_b + local; p < my_e; p += my_s * U) {
-            int col[U];
-            float v[U];
-            load_entries<VT, U, BT != DT_F32>(P.rem_col, P.rem_val, p, my_e, Ls, col, v);
-            gather_fma<BT, E, CPL, U>(col, v, p, my_e, a.B, rs, a.ldb, a.b_rec, cok, coff, Ls, a.cold_aux,
-                                      acc);
+        if constexpr (U < unroll_of<E, CPL>()) {
+            accumulate<VT, BT, E, CPL, U>(P.rem_col, P.rem_val, my_b, my_e, a.B, a.ldb, a.b_rec, cok, coff, Ls,
+                                          (g - local) * L.lpr, local, a.cold_aux, acc);
+        } else {
+            // (single runs, which hold 8 entries a step beside the pass's
+            // layout, keep their own loads: 100,000 rows, N = 128 of f16 75 us,
+            // held 78; 20,000 rows 25.2 / 26.8)
+            for (int p = my_b + local; p < my_e; p += my_s * U) {
+                int col[U];
+                float v[U];
+                load_entries<VT, U, BT != DT_F32>(P.rem_col, P.rem_val, p, my_e, Ls, col, v);
+                gather_fma<BT, E, CPL, U>(col, v, p, my_e, a.B, rs, a.ldb, a.b_rec, cok, coff, Ls, a.cold_aux,
+                                          acc);
+            }
         }
         // butterfly inside each block, from the pass's largest class down
         for (int off = (smax * L.lpr) >> 1; off >= L.lpr; off >>= 1) {
@@ -1129,10 +1219,20 @@ __device__ __forceinline__ void vector_item_classed(const DevPlan &P, const RunA
         i += k;
     }
 }
-template <int VT, int BT, int E, int CPL, int VAR, bool FUSED = false, int UL = unroll_of<E, CPL>()>
+// Waves per SIMD the kernels of vector items are compiled for, without which
+// held entries cost one (f32 B 88 registers for 80: graph of 2^20 rows, N = 128,
+// 925 us, bounded 900; more spills: 997 and up) or, in the batch's 16-bit
+// kernel, two (64 uneven f16 matrices: 1086 us, bounded 1015).
+template <int BT, int CPL, int VAR, int UL = 8, bool HOLD = true>
+constexpr int vector_waves() {
+    if (CPL != 1 || VAR < 2 || !HOLD) return 1;
+    return BT == DT_F32 ? 6 : UL < 8 ? 5 : 1;
+}
+
+template <int VT, int BT, int E, int CPL, int VAR, bool FUSED = false, int UL = unroll_of<E, CPL>(), bool HOLD = true>
 __device__ __forceinline__ void vector_item_var(const DevPlan &P, const RunArgs &a, int wid) {
     if constexpr (VAR == 3) vector_item_classed<VT, BT, E, CPL, FUSED, UL>(P, a, wid);
-    else if constexpr (VAR == 2) vector_item_packed<VT, BT, E, CPL, FUSED, UL>(P, a, wid);
+    else if constexpr (VAR == 2) vector_item_packed<VT, BT, E, CPL, FUSED, UL, HOLD>(P, a, wid);
     else if constexpr (VAR == 1) vector_item_pipelined<VT, BT, E, CPL, FUSED>(P, a, wid);
     else vector_item<VT, BT, E, CPL, FUSED>(P, a, wid);
 }

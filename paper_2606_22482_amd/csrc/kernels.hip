@@ -13,7 +13,7 @@ __global__ __launch_bounds__(256) void segment_kernel(DevPlan P, RunArgs a) {
 
 
 template <int VT, int BT, int E, int CPL, int VAR>
-__global__ __launch_bounds__(256) void vector_kernel(DevPlan P, RunArgs a) {
+__global__ __launch_bounds__(256, (vector_waves<BT, CPL, VAR>())) void vector_kernel(DevPlan P, RunArgs a) {
     const int wid = logical_block(a.xcd) * 4 + wave_id();
     if (wid < P.n_vitems * a.n_panels) vector_item_var<VT, BT, E, CPL, VAR>(P, a, wid);
 }
@@ -65,12 +65,18 @@ __global__ __launch_bounds__(256) void batch_segment_kernel(const BatchHeader *_
 template <int E, int CPL>
 constexpr int batch_unroll() { return (E == 8 && CPL == 1) ? 4 : unroll_of<E, CPL>(); }
 
+// The batch's rows of f32 B load their own entries: the small matrices of a
+// serving batch are bound by latency, and held entries add a hand-out to it (16
+// matrices of 1,000 to 20,000 rows: 164 us, held 174).
+template <int BT>
+constexpr bool batch_hold() { return BT != DT_F32; }
+
 template <int VT, int BT, int E, int CPL, int VAR>
-__global__ __launch_bounds__(256) void batch_vector_kernel(const BatchHeader *__restrict__ hdr,
+__global__ __launch_bounds__(256, (vector_waves<BT, CPL, VAR, batch_unroll<E, CPL>(), batch_hold<BT>()>())) void batch_vector_kernel(const BatchHeader *__restrict__ hdr,
                                                            const BatchEntry *__restrict__ tab) {
     const int sub = wave_id();
     SPMM_XCD_WALK(x_vec, vec_end, vec_base, 4,
-                  (vector_item_var<VT, BT, E, CPL, VAR, false, batch_unroll<E, CPL>()>(tab[d].P, tab[d].a, item)));
+                  (vector_item_var<VT, BT, E, CPL, VAR, false, batch_unroll<E, CPL>(), batch_hold<BT>()>(tab[d].P, tab[d].a, item)));
 }
 
 template <int VT, int BT, int TT, bool PARTIAL>
