@@ -1222,10 +1222,13 @@ __device__ __forceinline__ void vector_item_classed(const DevPlan &P, const RunA
 // Waves per SIMD the kernels of vector items are compiled for, without which
 // held entries cost one (f32 B 88 registers for 80: graph of 2^20 rows, N = 128,
 // 925 us, bounded 900; more spills: 997 and up) or, in the batch's 16-bit
-// kernel, two (64 uneven f16 matrices: 1086 us, bounded 1015).
+// kernel, two (64 uneven f16 matrices: 1086 us, bounded 1015).  Size classes
+// hold entries in the batch's half steps only (UL < 8); full steps need their 96
+// registers, and a bound of 80 spills 9 of them (f32, 200,000 rows, N = 128:
+// 202 us, unbounded 184).
 template <int BT, int CPL, int VAR, int UL = 8, bool HOLD = true>
 constexpr int vector_waves() {
-    if (CPL != 1 || VAR < 2 || !HOLD) return 1;
+    if (CPL != 1 || VAR < 2 || !HOLD || (VAR == 3 && UL >= 8)) return 1;
     return BT == DT_F32 ? 6 : UL < 8 ? 5 : 1;
 }
 
