@@ -404,16 +404,18 @@ __device__ __forceinline__ void gather_fma(const int (&col)[U], const float (&v)
                 // resource (a branch makes the compiler wait for each load
                 // before issuing the next): a masked entry or a chunk outside
                 // the panel loads at offset brec, out of the buffer's range,
-                // which returns zeros without a memory access.  Without one (B
-                // spanning 4 GiB or more, or 16-bit rows not aligned to 4
-                // bytes) every load is a plain one, a masked entry's from the
-                // row its column names (a row of B: its clamped entry's, or
-                // row 0), and its value is not used.
+                // which returns zeros without a memory access.  Without one:
+                // f32 B (spanning 4 GiB or more) takes predicated plain loads;
+                // 16-bit B (that, or rows not aligned to 4 bytes) plain loads
+                // throughout, a masked entry's from the row its clamped entry
+                // names (a row of B), whose value is not used.
                 (void)cold_aux;
                 if (brec != 0) {
                     load_raw_buf<BT, E>(rs, ok && cok[c] ? (uint32_t)(boff * SB) : brec, b[u][c]);
-                } else {
+                } else if (BT != DT_F32 || (ok && cok[c])) {
                     load_raw<BT, E, false>(B, boff, b[u][c]);
+                } else {
+                    zero_raw<BT, E>(b[u][c]);
                 }
             }
         }
