@@ -70,6 +70,7 @@ struct RunArgs {
     int32_t cold_aux;   // buffer-load policy bits for non-hot B rows; -1: plain loads for all
     uint32_t b_rec;     // bytes of B reachable through a buffer resource (its span); 0 when B
                         // spans 4 GiB or more or its chunks are not aligned to 4 bytes (plain loads)
+    int32_t hold;       // 1: kernels whose lanes hold the entries they sum (see make_run_args)
     int32_t pipeline;   // vector kernel variant: 0 row by row, 1 row-pipelined, 2 short rows packed,
                         // 3 rows packed by size class
     // co-scheduled execution

@@ -29,17 +29,18 @@ namespace spmm {
 // and in dispatch order across the XCDs (column-ordered segments then share
 // one stretch of B in the Infinity Cache), then the vector items, each XCD
 // taking consecutive items.
-template <int VT, int BT, int E, int CPL, int VAR>
+template <int VT, int BT, int E, int CPL, int VAR, bool HOLD>
 __device__ __forceinline__ void vector_path(const DevPlan &P, const RunArgs &a, int b) {
     if (b < a.seg_blocks) {
         const int wid = b * 4 + wave_id();
-        if (wid < P.n_seg * a.n_panels) segment_item<VT, BT, E, CPL, false, true>(P, a, wid);
+        if (wid < P.n_seg * a.n_panels) segment_item<VT, BT, E, CPL, false, true, HOLD>(P, a, wid);
     } else {
         const int j = b - a.seg_blocks;
         if (j >= a.vec_blocks) return;
         const int vb = a.xcd ? remap_block(j, a.vec_blocks) : j;
         const int wid = vb * 4 + wave_id();
-        if (wid < P.n_vitems * a.n_panels) vector_item_var<VT, BT, E, CPL, VAR, true>(P, a, wid);
+        if (wid < P.n_vitems * a.n_panels)
+            vector_item_var<VT, BT, E, CPL, VAR, true, unroll_of<E, CPL>(), HOLD>(P, a, wid);
     }
 }
 
@@ -57,9 +58,10 @@ __device__ __forceinline__ void mfma_path(const DevPlan &P, const RunArgs &a, in
         window_item<VT, BT, TT, MB, MBW, CW, BUF, true>(P, a, wid, partial);
 }
 
-template <int VT, int BT, int E, int CPL, int VAR>
-__global__ __launch_bounds__(256, (vector_waves<BT, CPL, VAR>())) void vector_path_kernel(DevPlan P, RunArgs a) {
-    vector_path<VT, BT, E, CPL, VAR>(P, a, blockIdx.x);
+template <int VT, int BT, int E, int CPL, int VAR, bool HOLD>
+__global__ __launch_bounds__(256, (vector_waves<BT, CPL, VAR, unroll_of<E, CPL>(), HOLD>())) void vector_path_kernel(
+    DevPlan P, RunArgs a) {
+    vector_path<VT, BT, E, CPL, VAR, HOLD>(P, a, blockIdx.x);
 }
 
 template <int VT, int BT, int TT, int MB, int MBW, int CW, bool BUF>
@@ -73,20 +75,20 @@ __global__ __launch_bounds__(256, 2) void one_grid_kernel(DevPlan P, RunArgs a) 
     const int wb = a.wpart_blocks + ((a.win_blocks + 7) & ~7);
     const int b = blockIdx.x;
     if (b < wb) mfma_path<VT, BT, TT, 0, 1, E, true>(P, a, b);
-    else vector_path<VT, BT, E, CPL, VAR>(P, a, b - wb);
+    else vector_path<VT, BT, E, CPL, VAR, true>(P, a, b - wb);
 }
 
 // ------------------------------------------------------------------------------------------
 // launchers
 
-template <int VT, int BT, int E, int CPL>
+template <int VT, int BT, int E, int CPL, bool HOLD>
 static hipError_t vp_var(const DevPlan &P, const RunArgs &a, hipStream_t s) {
     const dim3 grid((unsigned)(a.seg_blocks + a.vec_blocks)), block(256);
     switch (a.pipeline) {
-    case 3: launch_kernel((vector_path_kernel<VT, BT, E, CPL, 3>), grid, block, 0, s, P, a); break;
-    case 2: launch_kernel((vector_path_kernel<VT, BT, E, CPL, 2>), grid, block, 0, s, P, a); break;
-    case 1: launch_kernel((vector_path_kernel<VT, BT, E, CPL, 1>), grid, block, 0, s, P, a); break;
-    default: launch_kernel((vector_path_kernel<VT, BT, E, CPL, 0>), grid, block, 0, s, P, a); break;
+    case 3: launch_kernel((vector_path_kernel<VT, BT, E, CPL, 3, HOLD>), grid, block, 0, s, P, a); break;
+    case 2: launch_kernel((vector_path_kernel<VT, BT, E, CPL, 2, HOLD>), grid, block, 0, s, P, a); break;
+    case 1: launch_kernel((vector_path_kernel<VT, BT, E, CPL, 1, HOLD>), grid, block, 0, s, P, a); break;
+    default: launch_kernel((vector_path_kernel<VT, BT, E, CPL, 0, HOLD>), grid, block, 0, s, P, a); break;
     }
     return hipGetLastError();
 }
@@ -94,9 +96,10 @@ static hipError_t vp_var(const DevPlan &P, const RunArgs &a, hipStream_t s) {
 template <int VT, int BT>
 static hipError_t vp_types(const DevPlan &P, const RunArgs &a, hipStream_t s) {
     constexpr int EV = BT == DT_F32 ? 4 : 8;
-    if (!a.vec_ok) return vp_var<VT, BT, 1, 2>(P, a, s);
-    if ((a.np + EV - 1) / EV <= 64) return vp_var<VT, BT, EV, 1>(P, a, s);
-    return vp_var<VT, BT, EV, 2>(P, a, s);
+    if (!a.vec_ok) return vp_var<VT, BT, 1, 2, false>(P, a, s);
+    const bool one = (a.np + EV - 1) / EV <= 64;
+    if (a.hold) return one ? vp_var<VT, BT, EV, 1, true>(P, a, s) : vp_var<VT, BT, EV, 2, true>(P, a, s);
+    return one ? vp_var<VT, BT, EV, 1, false>(P, a, s) : vp_var<VT, BT, EV, 2, false>(P, a, s);
 }
 
 hipError_t launch_vector_path(const DevPlan &P, int32_t vt, int32_t bt, const RunArgs &a, hipStream_t s) {

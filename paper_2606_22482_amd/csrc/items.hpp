@@ -470,16 +470,16 @@ __device__ __forceinline__ void load_hold(const int32_t *__restrict__ rcol, cons
 // p0 + i taken by group i mod L.groups of the block, in increasing i (see the
 // file comment); `local` is this lane's group in the block, which starts at
 // lane `first`.
-template <int VT, int BT, int E, int CPL, int U, bool POL = false, bool HOLD = true>
+template <int VT, int BT, int E, int CPL, int U, bool POL, bool HOLD>
 __device__ __forceinline__ void accumulate(const int32_t *__restrict__ rcol, const void *__restrict__ rval, int p0,
                                            int p1, const void *__restrict__ B, int64_t ldb, uint32_t brec,
                                            const bool (&cok)[CPL], const int64_t (&coff)[CPL], const Lanes &L,
                                            int first, int local, int cold_aux, float (&acc)[CPL][E]) {
     const __amdgpu_buffer_rsrc_t rs = b_resource(B, brec);
     const int S = L.groups, step = S * U;
-    // Narrow rows load their own entries: a hold of theirs is no longer than a
-    // step, or (f32, fewer than 16 lanes a row) the hand-out costs more than
-    // the loads (20,000 rows, N = 32: 16.2 us, held 18.6).
+    // A batch's kernels hold entries at any width (single runs: make_run_args);
+    // narrow rows load their own: a hold of theirs is no longer than a step, or
+    // (f32, fewer than 16 lanes a row) the hand-out costs more than the loads.
     if (!HOLD || (BT == DT_F32 ? L.lpr < 2 * U : 2 * L.lpr < U)) {
         for (int p = p0 + local; p < p1; p += step) {
             int col[U];
@@ -537,7 +537,7 @@ __device__ __forceinline__ void accumulate(const int32_t *__restrict__ rcol, con
 }
 
 // The same for one row on the whole wavefront.
-template <int VT, int BT, int E, int CPL, int U, bool POL = false, bool HOLD = true>
+template <int VT, int BT, int E, int CPL, int U, bool POL, bool HOLD>
 __device__ __forceinline__ void seg_accumulate(const int32_t *__restrict__ rcol,
                                                const void *__restrict__ rval, int p0, int p1,
                                                const void *__restrict__ B, int64_t ldb, uint32_t brec,
@@ -551,7 +551,7 @@ __device__ __forceinline__ void seg_accumulate(const int32_t *__restrict__ rcol,
 
 // acc += sum over entries [p0, p1) of one row, all taken by this lane's group
 // in increasing order (each group works on its own row).
-template <int VT, int BT, int E, int CPL, int U, bool POL = false, bool HOLD = true>
+template <int VT, int BT, int E, int CPL, int U, bool POL, bool HOLD>
 __device__ __forceinline__ void row_accumulate_group(const int32_t *__restrict__ rcol,
                                                      const void *__restrict__ rval, int p0, int p1,
                                                      const void *__restrict__ B, int64_t ldb,
@@ -796,7 +796,7 @@ __device__ __forceinline__ void window_combine(const DevPlan &P, const RunArgs &
 // One segment (of one panel) per wavefront: wid in [0, n_seg * n_panels).
 // FUSED: the segment then arrives at its row's counter (a vector row) or its
 // window's counters (a window row), and the last arrival finishes the result.
-template <int VT, int BT, int E, int CPL, bool POL, bool FUSED = false>
+template <int VT, int BT, int E, int CPL, bool POL, bool FUSED, bool HOLD>
 __device__ __forceinline__ void segment_item(const DevPlan &P, const RunArgs &a, int wid) {
     const int panel = wid / P.n_seg, li = wid - panel * P.n_seg;
     const int sid = P.seg_order ? P.seg_order[li] : li;  // the partial's slot
@@ -807,9 +807,9 @@ __device__ __forceinline__ void segment_item(const DevPlan &P, const RunArgs &a,
     for (int c = 0; c < CPL; ++c)
 #pragma unroll
         for (int e = 0; e < E; ++e) acc[c][e] = 0.0f;
-    seg_accumulate<VT, BT, E, CPL, unroll_of<E, CPL>(), POL>(P.rem_col, P.rem_val, P.seg_begin[sid],
-                                                        P.seg_end[sid], a.B, a.ldb, a.b_rec, ncol0, ncols,
-                                                        L, a.cold_aux, acc);
+    seg_accumulate<VT, BT, E, CPL, unroll_of<E, CPL>(), POL, HOLD>(P.rem_col, P.rem_val, P.seg_begin[sid],
+                                                              P.seg_end[sid], a.B, a.ldb, a.b_rec, ncol0, ncols,
+                                                              L, a.cold_aux, acc);
     group_reduce<E, CPL>(acc, L);
     if (L.group == 0) {
 #pragma unroll
@@ -875,9 +875,9 @@ __device__ __forceinline__ void vector_item(const DevPlan &P, const RunArgs &a, 
 #pragma unroll
             for (int x = 0; x < E; ++x) acc[c][x] = 0.0f;
         if (e - b <= P.seg_len) {
-            seg_accumulate<VT, BT, E, CPL, unroll_of<E, CPL>(), true>(P.rem_col, P.rem_val, b, e, a.B,
-                                                                a.ldb, a.b_rec, ncol0, ncols, L, a.cold_aux,
-                                                                acc);
+            seg_accumulate<VT, BT, E, CPL, unroll_of<E, CPL>(), true, false>(P.rem_col, P.rem_val, b, e, a.B,
+                                                                       a.ldb, a.b_rec, ncol0, ncols, L,
+                                                                       a.cold_aux, acc);
             group_reduce<E, CPL>(acc, L);
         } else {
             if constexpr (FUSED) continue;
@@ -1000,7 +1000,7 @@ __device__ __forceinline__ int wave_inclusive_scan(int x) {
 // UL: entries per group and step; the short-row bound stays 2 unroll_of, so
 // the summation order (which depends only on a row's length) is the same for
 // any UL.
-template <int VT, int BT, int E, int CPL, bool FUSED = false, int UL = unroll_of<E, CPL>(), bool HOLD = true>
+template <int VT, int BT, int E, int CPL, bool FUSED, int UL, bool HOLD>
 __device__ __forceinline__ void vector_item_packed(const DevPlan &P, const RunArgs &a, int wid) {
     constexpr int U = UL;
     constexpr int SHORT = 2 * unroll_of<E, CPL>();
@@ -1186,7 +1186,7 @@ __device__ __forceinline__ void vector_item_classed(const DevPlan &P, const RunA
         Lanes Ls = L;
         Ls.groups = my_s;
         if constexpr (U < unroll_of<E, CPL>()) {
-            accumulate<VT, BT, E, CPL, U>(P.rem_col, P.rem_val, my_b, my_e, a.B, a.ldb, a.b_rec, cok, coff, Ls,
+            accumulate<VT, BT, E, CPL, U, false, true>(P.rem_col, P.rem_val, my_b, my_e, a.B, a.ldb, a.b_rec, cok, coff, Ls,
                                           (g - local) * L.lpr, local, a.cold_aux, acc);
         } else {
             // (single runs, which hold 8 entries a step beside the pass's
@@ -1228,13 +1228,13 @@ __device__ __forceinline__ void vector_item_classed(const DevPlan &P, const RunA
 // hold entries in the batch's half steps only (UL < 8); full steps need their 96
 // registers, and a bound of 80 spills 9 of them (f32, 200,000 rows, N = 128:
 // 202 us, unbounded 184).
-template <int BT, int CPL, int VAR, int UL = 8, bool HOLD = true>
+template <int BT, int CPL, int VAR, int UL, bool HOLD>
 constexpr int vector_waves() {
     if (CPL != 1 || VAR < 2 || !HOLD || (VAR == 3 && UL >= 8)) return 1;
     return BT == DT_F32 ? 6 : UL < 8 ? 5 : 1;
 }
 
-template <int VT, int BT, int E, int CPL, int VAR, bool FUSED = false, int UL = unroll_of<E, CPL>(), bool HOLD = true>
+template <int VT, int BT, int E, int CPL, int VAR, bool FUSED, int UL, bool HOLD>
 __device__ __forceinline__ void vector_item_var(const DevPlan &P, const RunArgs &a, int wid) {
     if constexpr (VAR == 3) vector_item_classed<VT, BT, E, CPL, FUSED, UL>(P, a, wid);
     else if constexpr (VAR == 2) vector_item_packed<VT, BT, E, CPL, FUSED, UL, HOLD>(P, a, wid);

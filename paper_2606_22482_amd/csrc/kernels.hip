@@ -5,17 +5,18 @@
 #include "items.hpp"
 namespace spmm {
 
-template <int VT, int BT, int E, int CPL, bool POL>
+template <int VT, int BT, int E, int CPL, bool POL, bool HOLD>
 __global__ __launch_bounds__(256) void segment_kernel(DevPlan P, RunArgs a) {
     const int wid = logical_block(a.xcd) * 4 + wave_id();
-    if (wid < P.n_seg * a.n_panels) segment_item<VT, BT, E, CPL, POL>(P, a, wid);
+    if (wid < P.n_seg * a.n_panels) segment_item<VT, BT, E, CPL, POL, false, HOLD>(P, a, wid);
 }
 
 
-template <int VT, int BT, int E, int CPL, int VAR>
-__global__ __launch_bounds__(256, (vector_waves<BT, CPL, VAR>())) void vector_kernel(DevPlan P, RunArgs a) {
+template <int VT, int BT, int E, int CPL, int VAR, bool HOLD>
+__global__ __launch_bounds__(256, (vector_waves<BT, CPL, VAR, unroll_of<E, CPL>(), HOLD>())) void vector_kernel(
+    DevPlan P, RunArgs a) {
     const int wid = logical_block(a.xcd) * 4 + wave_id();
-    if (wid < P.n_vitems * a.n_panels) vector_item_var<VT, BT, E, CPL, VAR>(P, a, wid);
+    if (wid < P.n_vitems * a.n_panels) vector_item_var<VT, BT, E, CPL, VAR, false, unroll_of<E, CPL>(), HOLD>(P, a, wid);
 }
 
 
@@ -53,7 +54,7 @@ template <int VT, int BT, int E, int CPL, bool POL>
 __global__ __launch_bounds__(256) void batch_segment_kernel(const BatchHeader *__restrict__ hdr,
                                                             const BatchEntry *__restrict__ tab) {
     const int sub = wave_id();
-    SPMM_XCD_WALK(x_seg, seg_end, seg_base, 4, (segment_item<VT, BT, E, CPL, POL>(tab[d].P, tab[d].a, item)));
+    SPMM_XCD_WALK(x_seg, seg_end, seg_base, 4, (segment_item<VT, BT, E, CPL, POL, false, !POL>(tab[d].P, tab[d].a, item)));
 }
 
 // Entries per group and step of the batched vector kernel: 4 for 16-bit B in
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(256) void copy_kernel(const f32x4 *__restrict__ src
 
 static inline unsigned grid_for_waves(int64_t waves) { return (unsigned)((waves + 3) / 4); }
 
-template <int VT, int BT, bool POL>
+template <int VT, int BT, bool POL, bool HOLD>
 static hipError_t seg_dispatch_pol(const DevPlan &P, const RunArgs &a, hipStream_t s) {
     const int64_t waves = (int64_t)P.n_seg * a.n_panels;
     if (waves == 0) return hipSuccess;
@@ -125,10 +126,10 @@ static hipError_t seg_dispatch_pol(const DevPlan &P, const RunArgs &a, hipStream
     const int chunks = a.vec_ok ? (a.np + EV - 1) / EV : a.np;
     dim3 grid(grid_for_waves(waves)), block(256);
     if (a.vec_ok) {
-        if (chunks <= 64) launch_kernel((segment_kernel<VT, BT, EV, 1, POL>), grid, block, 0, s, P, a);
-        else launch_kernel((segment_kernel<VT, BT, EV, 2, POL>), grid, block, 0, s, P, a);
+        if (chunks <= 64) launch_kernel((segment_kernel<VT, BT, EV, 1, POL, HOLD>), grid, block, 0, s, P, a);
+        else launch_kernel((segment_kernel<VT, BT, EV, 2, POL, HOLD>), grid, block, 0, s, P, a);
     } else {
-        launch_kernel((segment_kernel<VT, BT, 1, 2, POL>), grid, block, 0, s, P, a);
+        launch_kernel((segment_kernel<VT, BT, 1, 2, POL, false>), grid, block, 0, s, P, a);
     }
     return hipGetLastError();
 }
@@ -136,11 +137,11 @@ static hipError_t seg_dispatch_pol(const DevPlan &P, const RunArgs &a, hipStream
 template <int VT, int BT>
 static hipError_t seg_dispatch(const DevPlan &P, const RunArgs &a, hipStream_t s) {
     // the per-entry cache-policy choice only for plans with a cold policy
-    return a.cold_aux >= 0 ? seg_dispatch_pol<VT, BT, true>(P, a, s)
-                           : seg_dispatch_pol<VT, BT, false>(P, a, s);
+    if (a.cold_aux >= 0) return seg_dispatch_pol<VT, BT, true, false>(P, a, s);
+    return a.hold ? seg_dispatch_pol<VT, BT, false, true>(P, a, s) : seg_dispatch_pol<VT, BT, false, false>(P, a, s);
 }
 
-template <int VT, int BT, int VAR>
+template <int VT, int BT, int VAR, bool HOLD>
 static hipError_t vec_dispatch_var(const DevPlan &P, const RunArgs &a, hipStream_t s) {
     const int64_t waves = (int64_t)P.n_vitems * a.n_panels;
     if (waves == 0) return hipSuccess;
@@ -148,20 +149,21 @@ static hipError_t vec_dispatch_var(const DevPlan &P, const RunArgs &a, hipStream
     const int chunks = a.vec_ok ? (a.np + EV - 1) / EV : a.np;
     dim3 grid(grid_for_waves(waves)), block(256);
     if (a.vec_ok) {
-        if (chunks <= 64) launch_kernel((vector_kernel<VT, BT, EV, 1, VAR>), grid, block, 0, s, P, a);
-        else launch_kernel((vector_kernel<VT, BT, EV, 2, VAR>), grid, block, 0, s, P, a);
+        if (chunks <= 64) launch_kernel((vector_kernel<VT, BT, EV, 1, VAR, HOLD>), grid, block, 0, s, P, a);
+        else launch_kernel((vector_kernel<VT, BT, EV, 2, VAR, HOLD>), grid, block, 0, s, P, a);
     } else {
-        launch_kernel((vector_kernel<VT, BT, 1, 2, VAR>), grid, block, 0, s, P, a);
+        launch_kernel((vector_kernel<VT, BT, 1, 2, VAR, false>), grid, block, 0, s, P, a);
     }
     return hipGetLastError();
 }
 
 template <int VT, int BT>
 static hipError_t vec_dispatch(const DevPlan &P, const RunArgs &a, hipStream_t s) {
-    if (a.pipeline == 3) return vec_dispatch_var<VT, BT, 3>(P, a, s);
-    if (a.pipeline == 2) return vec_dispatch_var<VT, BT, 2>(P, a, s);
-    if (a.pipeline == 1) return vec_dispatch_var<VT, BT, 1>(P, a, s);
-    return vec_dispatch_var<VT, BT, 0>(P, a, s);
+    if (a.pipeline == 3) return vec_dispatch_var<VT, BT, 3, false>(P, a, s);
+    if (a.pipeline == 2)  // (the others' rows load their own entries)
+        return a.hold ? vec_dispatch_var<VT, BT, 2, true>(P, a, s) : vec_dispatch_var<VT, BT, 2, false>(P, a, s);
+    if (a.pipeline == 1) return vec_dispatch_var<VT, BT, 1, false>(P, a, s);
+    return vec_dispatch_var<VT, BT, 0, false>(P, a, s);
 }
 
 template <int VT, int BT, int TT>

@@ -602,6 +602,13 @@ static int ilog2_ceil(int x) {
     return l;
 }
 
+// Entries the segment and vector kernels gather (the windows gather their own rows').
+static int64_t vector_entries(const spmm_plan_t *p) {
+    const HostPlan &h = p->hp;
+    if (h.win_order.empty()) return h.nnz;
+    return (p->aux ? p->dev_nrem : (int64_t)h.rem_src.size()) - h.win_rem;
+}
+
 spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void *C, int64_t ldc,
                           RunArgs &a) {
     const HostPlan &h = p->hp;
@@ -641,6 +648,19 @@ spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void
     // sum every row as the packed-row variant does (one order for both at such
     // widths), and that variant is the faster one for f32 B
     a.pipeline = h.opts.pipeline == 3 && sb == 4 && N % E != 0 && N > 32 ? 2 : h.opts.pipeline;
+    // Entries held by the lanes that sum a row (or segment): rows of at least 16
+    // lanes, and a run that gathers 300 MB or more.  Below, the entry loads hide
+    // behind the waves' other latencies and the hand-out adds to them, and a row
+    // of fewer lanes hands out as often as it would load; f32 rows on a whole
+    // wavefront gain at any size (one load brings 64 of their entries).  Graphs of
+    // 16 entries a row, us, own loads / held:
+    //   f32, N = 64:  20,000 rows (82 MB) 20.6 / 21.7, 100,000 (410 MB) 56.0 / 50.2; N = 32: 2^20 rows 305 / 327
+    //   f32, N = 128: 20,000 (164 MB) 35.4 / 35.3, 50,000 (410 MB) 54.6 / 49.9; N = 512: 5,000 (164 MB) 47.2 / 40.3
+    //   f16, N = 128: 20,000 (82 MB) 22.5 / 25.2, 50,000 (205 MB) 50.8 / 52.5, 100,000 (410 MB) 71.7 / 66.7
+    //   f16, N = 256: 20,000 (164 MB) 41.4 / 42.4, 50,000 (410 MB) 83.9 / 82.6; N = 64 (8 lanes): 200,000 79.4 / 84.6
+    const int lanes = 1 << a.lpr_log2;
+    const double gathered = (double)vector_entries(p) * N * sb;
+    a.hold = a.vec_ok && a.cold_aux < 0 && lanes >= 16 && ((sb == 4 && lanes == 64) || gathered >= 300e6);
     // Window panels: 16 lanes of up to 16 bytes of a B row each (128 columns
     // of 16-bit B, 64 of f32), narrower for narrower N (a lane's chunk has to
     // fit in a row).  A wave takes all 64 rows of a high window, so that a B
