@@ -66,7 +66,8 @@ struct RunArgs {
     int32_t xcd;        // remap consecutive items onto one XCD
     int32_t win_panels; // panels of the window items (win_np columns each)
     int32_t win_np;     // columns per window panel: 16, 32, 64 or (16-bit B) 128
-    int32_t win_subs;   // waves of a window item, each with an equal share of its 16-row blocks
+    int32_t win_subs;   // waves of a window item, each with an equal share of its 16-row blocks, or
+    int32_t win_rows;   // (1) of a block's rows: rows that each of a wave's 4 lane groups takes, 4 or 1
     int32_t cold_aux;   // buffer-load policy bits for non-hot B rows; -1: plain loads for all
     uint32_t b_rec;     // bytes of B reachable through a buffer resource (its span); 0 when B
                         // spans 4 GiB or more or its chunks are not aligned to 4 bytes (plain loads)
@@ -155,34 +156,47 @@ hipError_t launch_vector_path(const DevPlan &P, int32_t val_t, int32_t b_t, cons
                               hipStream_t s);
 hipError_t launch_mfma_path(const DevPlan &P, int32_t val_t, int32_t b_t, int32_t tile_t,
                             const RunArgs &a, hipStream_t s);
-bool one_grid_supported(int32_t b_t, const RunArgs &a);
+bool one_grid_supported(const DevPlan &P, int32_t b_t, const RunArgs &a);
 hipError_t launch_one_grid(const DevPlan &P, int32_t val_t, int32_t b_t, int32_t tile_t,
                            const RunArgs &a, hipStream_t s);
 // p[0 .. n) = 0 by a kernel (capturable, unlike a memset node)
 hipError_t launch_zero(int32_t *p, int64_t n, hipStream_t s);
 
-// Calls f(MB, MBW, CW, BUF) (integral constants; see window_item) for the
+// Whether a run's waves of one 16-row block a window item (a fourth of one with
+// one row a lane group) are as many as its window height has: what a kernel of
+// such items takes its item and share from.
+inline bool one_block_waves(const DevPlan &P, const RunArgs &a) {
+    return 16 * a.win_subs == P.H * (a.win_rows == 1 ? 4 : 1);
+}
+
+// Calls f(MB, MBW, CW, BUF, RG) (integral constants; see window_item) for the
 // windows of a run: blocks of a window (0: taken from the plan), blocks a wave
-// takes, columns a lane takes, B through a buffer resource.
+// takes, columns a lane takes, B through a buffer resource, rows a lane group
+// takes.
 template <int BT, typename F>
 inline hipError_t window_shape(const DevPlan &P, const RunArgs &a, F &&f) {
     using std::integral_constant;
-    auto columns = [&](auto mb, auto mbw, auto buf) -> hipError_t {
+    const integral_constant<int, 4> four;
+    auto columns_rg = [&](auto mb, auto mbw, auto buf, auto rg) -> hipError_t {
         if constexpr (BT != 0)
-            if (a.win_np == 128) return f(mb, mbw, integral_constant<int, 8>{}, buf);
-        if (a.win_np == 64) return f(mb, mbw, integral_constant<int, 4>{}, buf);
-        if (a.win_np == 32) return f(mb, mbw, integral_constant<int, 2>{}, buf);
-        if constexpr (decltype(mbw)::value == 1)
-            if (a.win_np == 16) return f(mb, mbw, integral_constant<int, 1>{}, buf);
+            if (a.win_np == 128) return f(mb, mbw, integral_constant<int, 8>{}, buf, rg);
+        if (a.win_np == 64) return f(mb, mbw, integral_constant<int, 4>{}, buf, rg);
+        if (a.win_np == 32) return f(mb, mbw, integral_constant<int, 2>{}, buf, rg);
+        if constexpr (decltype(mbw)::value == 1 && decltype(rg)::value == 4)
+            if (a.win_np == 16) return f(mb, mbw, integral_constant<int, 1>{}, buf, rg);
         return hipErrorInvalidValue;
     };
+    auto columns = [&](auto mb, auto mbw, auto buf) { return columns_rg(mb, mbw, buf, four); };
     const integral_constant<int, 0> any;
     const integral_constant<int, 1> one;
     const integral_constant<int, 2> two;
-    const integral_constant<int, 4> four;
     const integral_constant<bool, true> buf;
     const integral_constant<bool, false> plain;
-    if (P.H == 16 * a.win_subs) {
+    if (a.win_rows == 1) {
+        if (!one_block_waves(P, a)) return hipErrorInvalidValue;
+        return a.b_rec ? columns_rg(any, one, buf, one) : columns_rg(any, one, plain, one);
+    }
+    if (one_block_waves(P, a)) {
         if (!a.b_rec) return columns(any, one, plain);
         return P.H == 16 ? columns(one, one, buf) : columns(any, one, buf);
     }

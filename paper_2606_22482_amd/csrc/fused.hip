@@ -46,7 +46,7 @@ __device__ __forceinline__ void vector_path(const DevPlan &P, const RunArgs &a, 
 
 // Workgroup b of the MFMA path: window partial items first, then the owners
 // (in window launch order, each XCD taking consecutive windows).
-template <int VT, int BT, int TT, int MB, int MBW, int CW, bool BUF>
+template <int VT, int BT, int TT, int MB, int MBW, int CW, bool BUF, int RG>
 __device__ __forceinline__ void mfma_path(const DevPlan &P, const RunArgs &a, int b) {
     const bool partial = b < a.wpart_blocks;
     // padding workgroups of the one-grid form (j beyond the range) stay idle:
@@ -55,7 +55,7 @@ __device__ __forceinline__ void mfma_path(const DevPlan &P, const RunArgs &a, in
     if (!partial && j >= a.win_blocks) return;
     const int wid = (!partial && a.xcd ? remap_block(j, a.win_blocks) : j) * 4 + wave_id();
     if (wid < (partial ? P.n_wpart : P.n_win) * a.win_panels * a.win_subs)
-        window_item<VT, BT, TT, MB, MBW, CW, BUF, true>(P, a, wid, partial);
+        window_item<VT, BT, TT, MB, MBW, CW, BUF, RG, true>(P, a, wid, partial);
 }
 
 template <int VT, int BT, int E, int CPL, int VAR, bool HOLD>
@@ -64,9 +64,9 @@ __global__ __launch_bounds__(256, (vector_waves<BT, CPL, VAR, unroll_of<E, CPL>(
     vector_path<VT, BT, E, CPL, VAR, HOLD>(P, a, blockIdx.x);
 }
 
-template <int VT, int BT, int TT, int MB, int MBW, int CW, bool BUF>
+template <int VT, int BT, int TT, int MB, int MBW, int CW, bool BUF, int RG>
 __global__ __launch_bounds__(256, (window_waves<MBW, CW>())) void mfma_path_kernel(DevPlan P, RunArgs a) {
-    mfma_path<VT, BT, TT, MB, MBW, CW, BUF>(P, a, blockIdx.x);
+    mfma_path<VT, BT, TT, MB, MBW, CW, BUF, RG>(P, a, blockIdx.x);
 }
 
 // The MFMA path's workgroups (padded to a multiple of 8), then the vector path's.
@@ -74,7 +74,7 @@ template <int VT, int BT, int TT, int E, int CPL, int VAR>
 __global__ __launch_bounds__(256, 2) void one_grid_kernel(DevPlan P, RunArgs a) {
     const int wb = a.wpart_blocks + ((a.win_blocks + 7) & ~7);
     const int b = blockIdx.x;
-    if (b < wb) mfma_path<VT, BT, TT, 0, 1, E, true>(P, a, b);
+    if (b < wb) mfma_path<VT, BT, TT, 0, 1, E, true, 4>(P, a, b);
     else vector_path<VT, BT, E, CPL, VAR, true>(P, a, b - wb);
 }
 
@@ -114,9 +114,9 @@ hipError_t launch_vector_path(const DevPlan &P, int32_t vt, int32_t bt, const Ru
 template <int VT, int BT, int TT>
 static hipError_t mp_types(const DevPlan &P, const RunArgs &a, hipStream_t s) {
     const dim3 grid((unsigned)(a.wpart_blocks + a.win_blocks)), block(256);
-    return window_shape<BT>(P, a, [&](auto mb, auto mbw, auto cw, auto buf) {
+    return window_shape<BT>(P, a, [&](auto mb, auto mbw, auto cw, auto buf, auto rg) {
         launch_kernel((mfma_path_kernel<VT, BT, TT, decltype(mb)::value, decltype(mbw)::value, decltype(cw)::value,
-                                        decltype(buf)::value>),
+                                        decltype(buf)::value, decltype(rg)::value>),
                       grid, block, 0, s, P, a);
         return hipGetLastError();
     });
@@ -148,15 +148,15 @@ static hipError_t og_types(const DevPlan &P, const RunArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-bool one_grid_supported(int32_t b_t, const RunArgs &a) {
+bool one_grid_supported(const DevPlan &P, int32_t b_t, const RunArgs &a) {
     const int ev = b_t == DT_F32 ? 4 : 8;
     return a.vec_ok && (a.np + ev - 1) / ev <= 64 && (a.pipeline == 2 || a.pipeline == 3) &&
-           a.win_np == 16 * ev && a.b_rec != 0;
+           a.win_np == 16 * ev && a.b_rec != 0 && a.win_rows == 4 && one_block_waves(P, a);
 }
 
 hipError_t launch_one_grid(const DevPlan &P, int32_t vt, int32_t bt, int32_t tt, const RunArgs &a,
                            hipStream_t s) {
-    if (!one_grid_supported(bt, a)) return hipErrorNotSupported;
+    if (!one_grid_supported(P, bt, a)) return hipErrorNotSupported;
     if (vt == DT_F32 && bt == DT_F32 && tt == DT_BF16) return og_types<DT_F32, DT_F32, DT_BF16>(P, a, s);
     if (vt == DT_F32 && bt == DT_BF16 && tt == DT_BF16) return og_types<DT_F32, DT_BF16, DT_BF16>(P, a, s);
     if (vt == DT_BF16 && bt == DT_BF16 && tt == DT_BF16) return og_types<DT_BF16, DT_BF16, DT_BF16>(P, a, s);

@@ -727,7 +727,8 @@ __device__ __forceinline__ int win_target(const DevPlan &P, const RunArgs &a, in
 template <int UN>
 __device__ __forceinline__ void window_combine(const DevPlan &P, const RunArgs &a, int w, int q, int dep,
                                                int sub) {
-    const int H = P.H, rows = H / a.win_subs;
+    const int H = P.H, rows = H / a.win_subs;  // (win_rows 1: rows sub % 4, + 4, + 8, + 12 of block sub / 4)
+    const int first = a.win_rows == 1 ? (sub >> 2) * 16 + (sub & 3) : sub * rows, step = a.win_rows == 1 ? 4 : 1;
     const int ncol0 = q * a.win_np, ncols = min(a.win_np, P.n - ncol0), nch = (ncols + 3) >> 2;
     const int pa = P.win_part[w], pb = P.win_part[w + 1];
     const int64_t ld = a.work_ld;
@@ -741,7 +742,7 @@ __device__ __forceinline__ void window_combine(const DevPlan &P, const RunArgs &
 #pragma unroll
         for (int i = 0; i < UN; ++i) {
             const int u = min(u0 + 64 * i, total - 1);
-            s[i] = sub * rows + u / nch;
+            s[i] = first + u / nch * step;
             c[i] = u % nch;
             r[i] = P.windows[(int64_t)w * H + s[i]];
             sid[i] = P.win_row_sid[(int64_t)w * H + s[i]];
@@ -1299,6 +1300,11 @@ __device__ __forceinline__ int row16_broadcast(int x) {
 // MBW 16-row blocks of the window, MB in all (MB = 0: the plan's, MBW = 1);
 // wid = item * (MB / MBW) + share, panel innermost, so a window's waves run
 // side by side and share its tiles and B rows in L1 and L2.
+// RG: rows of the block that each of the wave's 4 lane groups takes: all four of
+// its MFMA results', or (1: four shares a block, one wave each) row 4g + share %
+// 4 alone, 8 or 16 of whose remainder entries are in flight instead of 2 or 4.
+// Every share of a block multiplies its tiles.  (A row's sum is the same: its
+// entries are added one after the other.)
 //
 // A wave needs no LDS and no barrier: lane (g, c) = (lane / 16, lane % 16)
 // loads CW consecutive elements of the B rows 8g .. 8g+7 of a tile, which is
@@ -1339,15 +1345,17 @@ __device__ __forceinline__ int row16_broadcast(int x) {
 template <int MBW, int CW>
 constexpr int window_waves() { return MBW * CW == 32 ? 1 : MBW == 1 ? 3 : 2; }
 
-template <int VT, int BT, int TT, int MB, int MBW, int CW, bool BUF, bool FUSED = false>
+template <int VT, int BT, int TT, int MB, int MBW, int CW, bool BUF, int RG, bool FUSED = false>
 __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, int wid, bool partial) {
     static_assert(MB == 0 ? MBW == 1 : MB % MBW == 0, "a wave takes whole 16-row blocks");
+    static_assert(RG == 4 || (RG == 1 && MB == 0), "rows of a lane group");
     constexpr int NBUF = 2;
     constexpr bool ACC = MBW * CW == 32;
     constexpr int NPW = 16 * CW, SB = BT == DT_F32 ? 4 : 2;
     constexpr bool PRE = MBW == 1;  // the rows' remainder ranges are loaded with the first tiles
     const int H = MB ? MB * 16 : P.H;
-    const int subs_log2 = MB ? (MB / MBW == 4 ? 2 : MB / MBW == 2 ? 1 : 0) : (H >> 5);  // H 16, 32, 64
+    const int subs_log2 = (MB ? (MB / MBW == 4 ? 2 : MB / MBW == 2 ? 1 : 0) : (H >> 5))  // H 16, 32, 64
+                          + (RG == 1 ? 2 : 0);
     const int item = wid >> subs_log2, sub = wid & ((1 << subs_log2) - 1);
     const int j_item = item / a.win_panels, panel = item - j_item * a.win_panels;
     const int wi = partial ? P.wpart_win[j_item] : (P.win_order ? P.win_order[j_item] : j_item);
@@ -1357,7 +1365,8 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
     const int t1 = partial ? P.wpart_t1[j_item] : min(P.win_tile_ptr[wi + 1], t0 + P.win_tmax);
     const int start = ncol0 + min(l16 * CW, ncols - CW);  // this lane's columns start .. start + CW - 1
     const bool own = l16 * CW < ncols;
-    const int rb0 = sub * MBW;
+    const int rb0 = (RG == 1 ? sub >> 2 : sub) * MBW;  // first block
+    const int rq = RG == 1 ? sub & 3 : 0;              // first row of a lane group's (4g + rq ..)
     const __amdgpu_buffer_rsrc_t rs = b_resource(a.B, a.b_rec);
     const uint32_t ldbs = (uint32_t)(a.ldb * SB), sbyte = (uint32_t)(start * SB);
     const int64_t zoff = reinterpret_cast<const char *>(P.zeros) - static_cast<const char *>(a.B);
@@ -1376,17 +1385,23 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
     };
 
     typedef int i32x4 __attribute__((ext_vector_type(4)));
-    // rows 16 (rb0 + mb) + 4g .. + 3 of the window: id and remainder range
+    // rows 16 (rb0 + mb) + 4g + rq .. + RG - 1 of the window: id and remainder range
     struct Rows {
-        i32x4 r;
-        int b[4], e[4];
+        int r[RG], b[RG], e[RG];
     };
     auto row_ids = [&](int mb, Rows &R) {
-        R.r = *reinterpret_cast<const i32x4 *>(P.windows + (int64_t)wi * H + (rb0 + mb) * 16 + 4 * g);
+        const int32_t *w = P.windows + (int64_t)wi * H + (rb0 + mb) * 16 + 4 * g + rq;
+        if constexpr (RG == 4) {
+            const i32x4 r = *reinterpret_cast<const i32x4 *>(w);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) R.r[x] = r[x];
+        } else {
+            R.r[0] = *w;
+        }
     };
     auto row_ranges = [&](Rows &R) {
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
+        for (int x = 0; x < RG; ++x) {
             R.b[x] = P.rem_ptr[max(R.r[x], 0)];
             R.e[x] = P.rem_ptr[max(R.r[x], 0) + 1];
         }
@@ -1394,15 +1409,15 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
     auto split = [&](const Rows &R, int x) { return R.r[x] >= 0 && R.e[x] - R.b[x] > P.seg_len; };
     // end of the entries gathered here: none of a missing or a split row
     auto end = [&](const Rows &R, int x) { return R.r[x] < 0 || R.e[x] - R.b[x] > P.seg_len ? R.b[x] : R.e[x]; };
-    // entries u .. u + 15 of each of the 4 rows, one a lane of the row's group
+    // entries u .. u + 15 of each of the rows, one a lane of the row's group
     // (at clamped indices: the plan's arrays end in zeros)
     struct Entries {
-        int col[4];
-        float v[4];
+        int col[RG];
+        float v[RG];
     };
     auto entries = [&](const Rows &R, int u, Entries &q) {
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
+        for (int x = 0; x < RG; ++x) {
             const int p = max(min(R.b[x] + u + l16, end(R, x) - 1), 0);
             q.col[x] = __builtin_nontemporal_load(P.rem_col + p) & 0x7FFFFFFF;
             q.v[x] = load_val<VT>(P.rem_val, p);
@@ -1412,6 +1427,22 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
     // from lane u % 16 of the group
     auto has = [&](const Rows &R, int x, int u) { return R.b[x] + u < end(R, x); };
     auto from = [&](int v, int u) { return __builtin_amdgcn_ds_bpermute(((lane & 48) | (u & 15)) << 2, v); };
+    // entries 0 .. PE - 1 of every row, in the place of a tile's 8 rows a lane group
+    constexpr int PE = 8 / RG;
+    auto first8 = [&](const int (&q)[RG], int (&c)[8]) {
+        if constexpr (RG == 4) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                c[2 * x] = row16_broadcast<0>(q[x]);
+                c[2 * x + 1] = row16_broadcast<1>(q[x]);
+            }
+        } else {
+            c[0] = row16_broadcast<0>(q[0]); c[1] = row16_broadcast<1>(q[0]);
+            c[2] = row16_broadcast<2>(q[0]); c[3] = row16_broadcast<3>(q[0]);
+            c[4] = row16_broadcast<4>(q[0]); c[5] = row16_broadcast<5>(q[0]);
+            c[6] = row16_broadcast<6>(q[0]); c[7] = row16_broadcast<7>(q[0]);
+        }
+    };
 
     Rows R;
     Entries q0;
@@ -1436,11 +1467,10 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
         int col[8] = {row16_broadcast<0>(c), row16_broadcast<1>(c), row16_broadcast<2>(c), row16_broadcast<3>(c),
                       row16_broadcast<4>(c), row16_broadcast<5>(c), row16_broadcast<6>(c), row16_broadcast<7>(c)};
         if constexpr (REM) {
+            int rc[8];
+            first8(q0.col, rc);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {  // entries 0 and 1 of every row
-                const int x = i >> 1, c = i & 1 ? row16_broadcast<1>(q0.col[x]) : row16_broadcast<0>(q0.col[x]);
-                col[i] = t < t1 ? col[i] : some && has(R, x, i & 1) ? c : -1;
-            }
+            for (int i = 0; i < 8; ++i) col[i] = t < t1 ? col[i] : some && has(R, i / PE, i % PE) ? rc[i] : -1;
         }
         load_rows(col, x.b);
         __builtin_amdgcn_sched_barrier(0);
@@ -1491,7 +1521,7 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
     if constexpr (PRE) {
         bool any = false;
 #pragma unroll
-        for (int x = 0; x < 4; ++x) any |= !partial && has(R, x, 0);
+        for (int x = 0; x < RG; ++x) any |= !partial && has(R, x, 0);
         some = __any(any);
         if (some) entries(R, 0, q0);
     }
@@ -1525,6 +1555,15 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
             else st_dev1(ws, off + c, z[c]);
         }
     };
+    // the MFMA result of row x of this lane group
+    auto result = [&](int mb, int x, float (&z)[CW]) {
+#pragma unroll
+        for (int c = 0; c < CW; ++c) {
+            const f32x4 &v = acc[mb][c];
+            if constexpr (RG == 4) z[c] = v[x];
+            else z[c] = rq == 0 ? v[0] : rq == 1 ? v[1] : rq == 2 ? v[2] : v[3];
+        }
+    };
     if (partial || dep >= 0) {
         // the MFMA result of these tiles: for the owner item (or the last
         // arrival) to add, or the owner's own, kept in the window's slot
@@ -1534,11 +1573,10 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
 #pragma unroll
             for (int mb = 0; mb < MBW; ++mb)
 #pragma unroll
-                for (int x = 0; x < 4; ++x) {
+                for (int x = 0; x < RG; ++x) {
                     float z[CW];
-#pragma unroll
-                    for (int c = 0; c < CW; ++c) z[c] = acc[mb][c][x];
-                    const int64_t off = dst + (int64_t)((rb0 + mb) * 16 + 4 * g + x) * ld + start;
+                    result(mb, x, z);
+                    const int64_t off = dst + (int64_t)((rb0 + mb) * 16 + 4 * g + rq + x) * ld + start;
                     if constexpr (FUSED) {
                         st_ws(off, z);
                     } else {
@@ -1558,24 +1596,28 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
 
 #pragma unroll
     for (int mb = 0; mb < MBW; ++mb) {
-        float v[4][CW];
+        float v[RG][CW];
 #pragma unroll
-        for (int x = 0; x < 4; ++x)
+        for (int x = 0; x < RG; ++x)
 #pragma unroll
             for (int c = 0; c < CW; ++c) v[x][c] = 0.0f;
         int u = 0;
         if constexpr (PRE) {
             if (some) {
+                int q[RG], val[8];
+#pragma unroll
+                for (int r = 0; r < RG; ++r) q[r] = __float_as_int(q0.v[r]);
+                first8(q, val);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    const int r = i >> 1, k = __float_as_int(q0.v[r]);
-                    const float val = __int_as_float(i & 1 ? row16_broadcast<1>(k) : row16_broadcast<0>(k));
-                    if (has(R, r, i & 1)) {
+                    const int r = i / PE;
+                    if (has(R, r, i % PE)) {
 #pragma unroll
-                        for (int c = 0; c < CW; ++c) v[r][c] = __builtin_fmaf(val, x[0].b[i].f32(c), v[r][c]);
+                        for (int c = 0; c < CW; ++c)
+                            v[r][c] = __builtin_fmaf(__int_as_float(val[i]), x[0].b[i].f32(c), v[r][c]);
                     }
                 }
-                u = 2;
+                u = PE;
             }
         } else {
             row_ids(mb, R);
@@ -1584,22 +1626,22 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
         auto more = [&] {
             bool any = false;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) any |= has(R, r, u);
+            for (int r = 0; r < RG; ++r) any |= has(R, r, u);
             return __any(any);
         };
         // the rest, RE entries of every row at a time, the next 16 entries in
         // flight with the last of these.  4 entries, 2 where their chunks would
         // spill: 64 registers of chunks for any width (16 entries at 32 columns)
         // cost 38,624 rows in blocks (2.2 entries a row), N = 32, 18.8 us for 8.1.
-        constexpr int RE = MBW == 1 && CW == 8 ? 2 : 4;
+        constexpr int CH = MBW == 1 && CW == 8 && RG == 4 ? 8 : 16, RE = CH / RG;
         if (more()) {
             if (!PRE) entries(R, 0, q0);
             do {
-                Chunk<BT, CW> rows[RE / 2][8];
-                float val[4 * RE];
+                Chunk<BT, CW> rows[CH / 8][8];
+                float val[CH];
                 const int u0 = u;
 #pragma unroll
-                for (int i = 0; i < RE / 2; ++i) {
+                for (int i = 0; i < CH / 8; ++i) {
                     int col[8];
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
@@ -1614,7 +1656,7 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
                 u = u1;
                 if ((u1 & 15) == 0) entries(R, u1, q0);
 #pragma unroll
-                for (int i = 0; i < 4 * RE; ++i) {
+                for (int i = 0; i < CH; ++i) {
                     const int r = i / RE, w = u0 + i % RE;
                     if (w < u1 && has(R, r, w)) {
 #pragma unroll
@@ -1625,8 +1667,8 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
             } while (more());
         }
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            const int s = (rb0 + mb) * 16 + 4 * g + x;
+        for (int x = 0; x < RG; ++x) {
+            const int s = (rb0 + mb) * 16 + 4 * g + rq + x;
             if (R.r[x] < 0 || !own) continue;
             if (dep >= 0) {
                 // the row's remainder, for the combine (a split row's is
@@ -1635,8 +1677,7 @@ __device__ __forceinline__ void window_item(const DevPlan &P, const RunArgs &a, 
                 continue;
             }
             float z[CW];
-#pragma unroll
-            for (int c = 0; c < CW; ++c) z[c] = acc[mb][c][x];
+            result(mb, x, z);
             if constexpr (!FUSED) {
                 // the window's other tiles' partial results, in tile order
                 // (fused: a window with partial items has a slot)

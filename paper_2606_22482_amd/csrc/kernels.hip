@@ -20,11 +20,11 @@ __global__ __launch_bounds__(256, (vector_waves<BT, CPL, VAR, unroll_of<E, CPL>(
 }
 
 
-template <int VT, int BT, int TT, int MB, int MBW, int CW, bool BUF>
+template <int VT, int BT, int TT, int MB, int MBW, int CW, bool BUF, int RG>
 __global__ __launch_bounds__(256, (window_waves<MBW, CW>())) void window_kernel(DevPlan P, RunArgs a, int partial) {
     const int wid = logical_block(a.xcd) * 4 + wave_id();
     if (wid < (partial ? P.n_wpart : P.n_win) * a.win_panels * a.win_subs)
-        window_item<VT, BT, TT, MB, MBW, CW, BUF>(P, a, wid, partial != 0);
+        window_item<VT, BT, TT, MB, MBW, CW, BUF, RG>(P, a, wid, partial != 0);
 }
 
 
@@ -84,15 +84,15 @@ template <int VT, int BT, int TT, bool PARTIAL>
 __device__ __forceinline__ void batch_window_item(const BatchEntry &e, int wid) {
     if constexpr (BT != DT_F32)
         if (e.a.win_np == 128)
-            return e.a.b_rec ? window_item<VT, BT, TT, 0, 1, 8, true>(e.P, e.a, wid, PARTIAL)
-                             : window_item<VT, BT, TT, 0, 1, 8, false>(e.P, e.a, wid, PARTIAL);
+            return e.a.b_rec ? window_item<VT, BT, TT, 0, 1, 8, true, 4>(e.P, e.a, wid, PARTIAL)
+                             : window_item<VT, BT, TT, 0, 1, 8, false, 4>(e.P, e.a, wid, PARTIAL);
     if (e.a.win_np == 64)
-        return e.a.b_rec ? window_item<VT, BT, TT, 0, 1, 4, true>(e.P, e.a, wid, PARTIAL)
-                         : window_item<VT, BT, TT, 0, 1, 4, false>(e.P, e.a, wid, PARTIAL);
+        return e.a.b_rec ? window_item<VT, BT, TT, 0, 1, 4, true, 4>(e.P, e.a, wid, PARTIAL)
+                         : window_item<VT, BT, TT, 0, 1, 4, false, 4>(e.P, e.a, wid, PARTIAL);
     if (e.a.win_np == 32)
-        return e.a.b_rec ? window_item<VT, BT, TT, 0, 1, 2, true>(e.P, e.a, wid, PARTIAL)
-                         : window_item<VT, BT, TT, 0, 1, 2, false>(e.P, e.a, wid, PARTIAL);
-    window_item<VT, BT, TT, 0, 1, 1, false>(e.P, e.a, wid, PARTIAL);
+        return e.a.b_rec ? window_item<VT, BT, TT, 0, 1, 2, true, 4>(e.P, e.a, wid, PARTIAL)
+                         : window_item<VT, BT, TT, 0, 1, 2, false, 4>(e.P, e.a, wid, PARTIAL);
+    window_item<VT, BT, TT, 0, 1, 1, false, 4>(e.P, e.a, wid, PARTIAL);
 }
 
 template <int VT, int BT, int TT, bool PARTIAL>
@@ -170,9 +170,9 @@ template <int VT, int BT, int TT>
 static hipError_t win_dispatch(const DevPlan &P, const RunArgs &a, hipStream_t s, bool partial) {
     const int64_t waves = (int64_t)(partial ? P.n_wpart : P.n_win) * a.win_panels * a.win_subs;
     if (waves == 0) return hipSuccess;
-    return window_shape<BT>(P, a, [&](auto mb, auto mbw, auto cw, auto buf) {
+    return window_shape<BT>(P, a, [&](auto mb, auto mbw, auto cw, auto buf, auto rg) {
         launch_kernel((window_kernel<VT, BT, TT, decltype(mb)::value, decltype(mbw)::value, decltype(cw)::value,
-                                     decltype(buf)::value>),
+                                     decltype(buf)::value, decltype(rg)::value>),
                       dim3(grid_for_waves(waves)), dim3(256), 0, s, P, a, partial ? 1 : 0);
         return hipGetLastError();
     });

@@ -675,21 +675,43 @@ spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void
     // 3,001, N = 128 (94, partial items): 43 / 25 / 19, 27 / 18 / 13, of 32: 19 / 13 / 12.
     // Short windows keep the matrix units less busy than the loads around them
     // and take two waves at once (100,000 rows in blocks, N = 128, 13 tiles a
-    // window: 59 / 50 / 62).  Where a window gathers more B rows for its
-    // remainders than for its tiles, panels of 64 columns, which hold twice the
-    // entries in flight a row (graph of 500,000 rows, 90 entries a row beside
-    // the tiles, N = 128 of bf16: MFMA path 206 us in panels of 128, 142 of 64).
+    // window: 59 / 50 / 62).
     a.win_np = N == 1 ? 16 : N <= 32 ? 32 : N <= 64 || sb == 4 ? 64 : 128;
+    a.win_rows = 4;
     const int mb = h.opts.window_h / 16;
     const int64_t items = (int64_t)p->dp.n_win + p->dp.n_wpart;
     const int64_t want = p->dp.n_wpart > 0 ? 1100 : 700;
     auto waves = [&] { return items * ((N + a.win_np - 1) / a.win_np) * a.win_subs; };
-    // (one block a wave where the kernels take no more: see window_shape)
-    a.win_subs = mb == 4 && N > 1 && h.opts.exec != 3 && (a.b_rec != 0 || sb == 2) ? 1 : mb;
-    if (a.win_np == 128 && (waves() < want || h.win_rem > (int64_t)p->dp.n_tiles * h.opts.kt)) a.win_np = 64;
-    if (a.win_subs < mb && p->dp.n_tiles < 32 * items) a.win_subs = 2;
-    while (a.win_subs < mb && waves() < want) a.win_subs *= 2;
-    if (a.win_np == 64 && N > 32 && waves() < (mb == 1 ? 1600 : want)) a.win_np = 32;
+    // Windows that gather more B rows for their remainders than for their tiles
+    // take the widest panels and one block a wave: a wave sums its rows'
+    // remainders side by side, as long as the longest of them, and a 64-row
+    // wave would do so four times. With few waves a lane group is left one row
+    // of four (items.hpp), though each of the four waves of a block then
+    // multiplies the block's tiles. Graphs of 16 entries a row (rows of more
+    // than 8 in windows), us, 4 / 1 rows a lane group (remainder rows for each
+    // tile row, waves of 4 rows a lane group; f32 panels of 64 give twice as many):
+    //   f16, N = 128: 20,000 rows, H = 16 (4.2, 240) 132 / 71; H = 64 in row order (5.5, 1240) 115 / 97
+    //   f16, N = 128: 100,000, H = 16 (4.3, 794) 160 / 106; H = 32 (4.6, 1666) 165 / 131; H = 64 (4.1, 1772) 178 / 162
+    //   f16, N = 256: 300,000, H = 32 (5.0, 7172) 488 / 599; H = 64 (4.8, 10216) 565 / 749
+    //   f32, N = 128: 20,000, H = 16 (4.1, 380) 64 / 49; 100,000, H = 32 (5.5, 2326) 150 / 158
+    // 16-row blocks of 8 at 30% with stray entries, N = 128:
+    //   f16: 20,000 rows (1250 waves) (1.0) 16 / 20, (3.0) 29 / 29, (5.2) 47 / 43; 4,096 (2.3, 256) 18 / 11
+    //   f32: 20,000 (3.0, 2500) 41 / 46; 4,096 (2.3, 512) 18 / 13
+    const int64_t tile_rows = (int64_t)p->dp.n_tiles * h.opts.kt;
+    if (N > 1 && h.win_rem > tile_rows) {
+        a.win_subs = mb;
+        if (waves() < (sb == 2 && h.win_rem > 3 * tile_rows ? 5000 : 700)) {
+            a.win_rows = 1;
+            a.win_subs = 4 * mb;
+        }
+    } else {
+        // (one block a wave where the kernels take no more: see window_shape)
+        a.win_subs = mb == 4 && N > 1 && h.opts.exec != 3 && (a.b_rec != 0 || sb == 2) ? 1 : mb;
+        if (a.win_np == 128 && waves() < want) a.win_np = 64;
+        if (a.win_subs < mb && p->dp.n_tiles < 32 * items) a.win_subs = 2;
+        while (a.win_subs < mb && waves() < want) a.win_subs *= 2;
+        if (a.win_np == 64 && N > 32 && waves() < (mb == 1 ? 1600 : want)) a.win_np = 32;
+    }
     a.win_panels = (N + a.win_np - 1) / a.win_np;
     return SPMM_OK;
 }
@@ -868,7 +890,7 @@ spmm_status launch_plan(const spmm_plan_t *p, const RunArgs &a0, hipStream_t s, 
         return timed(SPMM_KERNEL_WINDOW, s,
                      [&] { return launch_window(P, h.val_type, h.b_type, h.tile_type, a, s, false); });
     }
-    if (h.opts.exec == 3 && mfma && vec && one_grid_supported(h.b_type, a))
+    if (h.opts.exec == 3 && mfma && vec && one_grid_supported(P, h.b_type, a))
         return timed(SPMM_KERNEL_ONE_GRID, s,
                      [&] { return launch_one_grid(P, h.val_type, h.b_type, h.tile_type, a, s); });
     const bool fork = ctx.allow_fork && fork_paths(a);

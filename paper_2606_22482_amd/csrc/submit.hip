@@ -129,6 +129,7 @@ extern "C" spmm_status spmm_submit(const spmm_work *items, int32_t count, void *
         const spmm_plan_t *p = items[i].plan;
         if (p->hp.m == 0) continue;
         make_run_args(p, items[i].B, items[i].ldb, items[i].C, items[i].ldc, args[i]);
+        args[i].win_rows = 4;
         args[i].win_subs = p->hp.opts.window_h / 16;  // the batched window kernels' waves take one 16-row block
         ws_floats += workspace_floats(p->hp, true);
         const int E = args[i].vec_ok ? chunk_elems(p->hp.b_type) : 1;
