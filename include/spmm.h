@@ -139,7 +139,9 @@ typedef struct {
                           vector items) and the MFMA path (window partials and owners) as two grids that
                           run concurrently on the run's stream and a second stream of it (fork and join
                           by events, so a graph capture of the run records both); 3 = co-scheduled in one
-                          grid.  In 2 and 3 a result needing several items (a split row, a window with
+                          grid, for plans with windows and vector rows, pipeline 2 or 3 and, in a
+                          panel, 4 to 256 columns of f32 B or (N > 64) up to 512 of 16-bit B; the
+                          others run as 2.  In 2 and 3 a result needing several items (a split row, a window with
                           partial tiles or split rows) is finished by its last contributor, through
                           integer counters in the workspace; C is bitwise the same in all three.  A cold
                           policy needs 1.  <= 0: auto */

@@ -70,12 +70,15 @@ __global__ __launch_bounds__(256, (window_waves<MBW, CW>())) void mfma_path_kern
 }
 
 // The MFMA path's workgroups (padded to a multiple of 8), then the vector path's.
-template <int VT, int BT, int TT, int E, int CPL, int VAR>
-__global__ __launch_bounds__(256, 2) void one_grid_kernel(DevPlan P, RunArgs a) {
+// Bounded to 4 waves per SIMD with one row a lane group (133 to 143 registers
+// without; f32, 200,000 rows, N = 64: 149 -> 124 us); the windows' registers
+// leave no room for held entries beside them.
+template <int VT, int BT, int TT, int E, int CPL, int VAR, bool BUF, int RG>
+__global__ __launch_bounds__(256, RG == 1 ? 4 : 2) void one_grid_kernel(DevPlan P, RunArgs a) {
     const int wb = a.wpart_blocks + ((a.win_blocks + 7) & ~7);
     const int b = blockIdx.x;
-    if (b < wb) mfma_path<VT, BT, TT, 0, 1, E, true, 4>(P, a, b);
-    else vector_path<VT, BT, E, CPL, VAR, true>(P, a, b - wb);
+    if (b < wb) mfma_path<VT, BT, TT, 0, 1, E, BUF, RG>(P, a, b);
+    else vector_path<VT, BT, E, CPL, VAR, false>(P, a, b - wb);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -134,24 +137,33 @@ hipError_t launch_mfma_path(const DevPlan &P, int32_t vt, int32_t bt, int32_t tt
 
 // One grid: built for 16-byte chunks with one chunk per lane, the packed
 // vector variants (2, 3), which cover the defaults, and window panels of one
-// such chunk a lane; other plans report hipErrorNotSupported and run as two
-// grids.
+// such chunk a lane (make_run_args chooses them for a run that can take this
+// form); other plans report hipErrorNotSupported and run as two grids.
+template <int VT, int BT, int TT, int VAR>
+static hipError_t og_var(const DevPlan &P, const RunArgs &a, dim3 grid, hipStream_t s) {
+    constexpr int EV = BT == DT_F32 ? 4 : 8;
+    const dim3 block(256);
+    if (!a.b_rec) {
+        if (a.win_rows == 4) launch_kernel((one_grid_kernel<VT, BT, TT, EV, 1, VAR, false, 4>), grid, block, 0, s, P, a);
+        else launch_kernel((one_grid_kernel<VT, BT, TT, EV, 1, VAR, false, 1>), grid, block, 0, s, P, a);
+    } else {
+        if (a.win_rows == 4) launch_kernel((one_grid_kernel<VT, BT, TT, EV, 1, VAR, true, 4>), grid, block, 0, s, P, a);
+        else launch_kernel((one_grid_kernel<VT, BT, TT, EV, 1, VAR, true, 1>), grid, block, 0, s, P, a);
+    }
+    return hipGetLastError();
+}
+
 template <int VT, int BT, int TT>
 static hipError_t og_types(const DevPlan &P, const RunArgs &a, hipStream_t s) {
-    constexpr int EV = BT == DT_F32 ? 4 : 8;
     const unsigned wb = (unsigned)(a.wpart_blocks + ((a.win_blocks + 7) & ~7));
-    const dim3 grid(wb + (unsigned)(a.seg_blocks + a.vec_blocks)), block(256);
-    if (a.pipeline == 3)
-        launch_kernel((one_grid_kernel<VT, BT, TT, EV, 1, 3>), grid, block, 0, s, P, a);
-    else
-        launch_kernel((one_grid_kernel<VT, BT, TT, EV, 1, 2>), grid, block, 0, s, P, a);
-    return hipGetLastError();
+    const dim3 grid(wb + (unsigned)(a.seg_blocks + a.vec_blocks));
+    return a.pipeline == 3 ? og_var<VT, BT, TT, 3>(P, a, grid, s) : og_var<VT, BT, TT, 2>(P, a, grid, s);
 }
 
 bool one_grid_supported(const DevPlan &P, int32_t b_t, const RunArgs &a) {
     const int ev = b_t == DT_F32 ? 4 : 8;
     return a.vec_ok && (a.np + ev - 1) / ev <= 64 && (a.pipeline == 2 || a.pipeline == 3) &&
-           a.win_np == 16 * ev && a.b_rec != 0 && a.win_rows == 4 && one_block_waves(P, a);
+           a.win_np == 16 * ev && one_block_waves(P, a);
 }
 
 hipError_t launch_one_grid(const DevPlan &P, int32_t vt, int32_t bt, int32_t tt, const RunArgs &a,

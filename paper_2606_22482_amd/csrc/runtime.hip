@@ -698,15 +698,24 @@ spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void
     //   f16: 20,000 rows (1250 waves) (1.0) 16 / 20, (3.0) 29 / 29, (5.2) 47 / 43; 4,096 (2.3, 256) 18 / 11
     //   f32: 20,000 (3.0, 2500) 41 / 46; 4,096 (2.3, 512) 18 / 13
     const int64_t tile_rows = (int64_t)p->dp.n_tiles * h.opts.kt;
-    if (N > 1 && h.win_rem > tile_rows) {
+    // The one-grid kernels take panels of 16 bytes a lane and one block a wave.
+    // With one row a lane group they fit 4 waves per SIMD for 3, which counts
+    // where the vector rows outweigh the windows (f32, 200,000 rows, N = 128, one
+    // grid, four rows / one: 25 vector entries for each of the windows' 230 / 207
+    // us, 2 for each 223 / 241).
+    const bool one = h.opts.exec == 3 && a.vec_ok && chunks <= 64 && a.pipeline >= 2 && (sb == 4 || N > 64) &&
+                     p->dp.n_vitems + p->dp.n_seg > 0;
+    if (one) a.win_np = 16 * E;
+    if (one || (N > 1 && h.win_rem > tile_rows)) {
         a.win_subs = mb;
-        if (waves() < (sb == 2 && h.win_rem > 3 * tile_rows ? 5000 : 700)) {
+        if (h.win_rem > tile_rows && ((one && vector_entries(p) > 4 * h.win_rem) ||
+                                       waves() < (sb == 2 && h.win_rem > 3 * tile_rows ? 5000 : 700))) {
             a.win_rows = 1;
             a.win_subs = 4 * mb;
         }
     } else {
         // (one block a wave where the kernels take no more: see window_shape)
-        a.win_subs = mb == 4 && N > 1 && h.opts.exec != 3 && (a.b_rec != 0 || sb == 2) ? 1 : mb;
+        a.win_subs = mb == 4 && N > 1 && (a.b_rec != 0 || sb == 2) ? 1 : mb;
         if (a.win_np == 128 && waves() < want) a.win_np = 64;
         if (a.win_subs < mb && p->dp.n_tiles < 32 * items) a.win_subs = 2;
         while (a.win_subs < mb && waves() < want) a.win_subs *= 2;
