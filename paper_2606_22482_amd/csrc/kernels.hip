@@ -80,18 +80,32 @@ __global__ __launch_bounds__(256, (vector_waves<BT, CPL, VAR, batch_unroll<E, CP
                   (vector_item_var<VT, BT, E, CPL, VAR, false, batch_unroll<E, CPL>(), batch_hold<BT>()>(tab[d].P, tab[d].a, item)));
 }
 
+// An item of a batch: one 16-row block a wave, two (of 64-row windows of 16-bit
+// B), or one row a lane group; 172 registers without the last two, and with them
+// 237, which the same 2 waves per SIMD hold.
+template <int VT, int BT, int TT, int MB, int MBW, int CW, int RG>
+__device__ __forceinline__ void batch_window_shape(const BatchEntry &e, int wid, bool partial) {
+    if (e.a.b_rec) window_item<VT, BT, TT, MB, MBW, CW, true, RG>(e.P, e.a, wid, partial);
+    else window_item<VT, BT, TT, MB, MBW, CW, false, RG>(e.P, e.a, wid, partial);
+}
+
 template <int VT, int BT, int TT, bool PARTIAL>
 __device__ __forceinline__ void batch_window_item(const BatchEntry &e, int wid) {
-    if constexpr (BT != DT_F32)
-        if (e.a.win_np == 128)
-            return e.a.b_rec ? window_item<VT, BT, TT, 0, 1, 8, true, 4>(e.P, e.a, wid, PARTIAL)
-                             : window_item<VT, BT, TT, 0, 1, 8, false, 4>(e.P, e.a, wid, PARTIAL);
-    if (e.a.win_np == 64)
-        return e.a.b_rec ? window_item<VT, BT, TT, 0, 1, 4, true, 4>(e.P, e.a, wid, PARTIAL)
-                         : window_item<VT, BT, TT, 0, 1, 4, false, 4>(e.P, e.a, wid, PARTIAL);
-    if (e.a.win_np == 32)
-        return e.a.b_rec ? window_item<VT, BT, TT, 0, 1, 2, true, 4>(e.P, e.a, wid, PARTIAL)
-                         : window_item<VT, BT, TT, 0, 1, 2, false, 4>(e.P, e.a, wid, PARTIAL);
+    const int np = e.a.win_np;
+    if (e.a.win_rows == 1) {
+        if constexpr (BT != DT_F32)
+            if (np == 128) return batch_window_shape<VT, BT, TT, 0, 1, 8, 1>(e, wid, PARTIAL);
+        if (np == 64) return batch_window_shape<VT, BT, TT, 0, 1, 4, 1>(e, wid, PARTIAL);
+        return batch_window_shape<VT, BT, TT, 0, 1, 2, 1>(e, wid, PARTIAL);
+    }
+    if constexpr (BT != DT_F32) {
+        if (16 * e.a.win_subs < e.P.H)
+            return np == 128 ? batch_window_shape<VT, BT, TT, 4, 2, 8, 4>(e, wid, PARTIAL)
+                             : batch_window_shape<VT, BT, TT, 4, 2, 4, 4>(e, wid, PARTIAL);
+        if (np == 128) return batch_window_shape<VT, BT, TT, 0, 1, 8, 4>(e, wid, PARTIAL);
+    }
+    if (np == 64) return batch_window_shape<VT, BT, TT, 0, 1, 4, 4>(e, wid, PARTIAL);
+    if (np == 32) return batch_window_shape<VT, BT, TT, 0, 1, 2, 4>(e, wid, PARTIAL);
     window_item<VT, BT, TT, 0, 1, 1, false, 4>(e.P, e.a, wid, PARTIAL);
 }
 

@@ -610,7 +610,7 @@ static int64_t vector_entries(const spmm_plan_t *p) {
 }
 
 spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void *C, int64_t ldc,
-                          RunArgs &a) {
+                          RunArgs &a, int64_t beside) {
     const HostPlan &h = p->hp;
     const int N = h.n;
     const int E = chunk_elems(h.b_type);
@@ -681,7 +681,7 @@ spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void
     const int mb = h.opts.window_h / 16;
     const int64_t items = (int64_t)p->dp.n_win + p->dp.n_wpart;
     const int64_t want = p->dp.n_wpart > 0 ? 1100 : 700;
-    auto waves = [&] { return items * ((N + a.win_np - 1) / a.win_np) * a.win_subs; };
+    auto waves = [&] { return (items + beside) * ((N + a.win_np - 1) / a.win_np) * a.win_subs; };
     // Windows that gather more B rows for their remainders than for their tiles
     // take the widest panels and one block a wave: a wave sums its rows'
     // remainders side by side, as long as the longest of them, and a 64-row

@@ -72,8 +72,9 @@ void coschedule_layout(const spmm_plan_t *p, RunArgs &a);
 bool fork_paths(const RunArgs &a);
 // Arrival counters a run of the plan uses (0 when serial).
 size_t counter_ints(const spmm_plan_t *p, const RunArgs &a);
+// `beside`: window items of the other plans that run with it (a batch).
 spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void *C, int64_t ldc,
-                          RunArgs &a);
+                          RunArgs &a, int64_t beside = 0);
 spmm_status check_run(const spmm_plan_t *p, const void *B, int64_t ldb, void *C, int64_t ldc);
 spmm_status launch_plan(const spmm_plan_t *p, const RunArgs &a, hipStream_t s, spmm_timer_t *t,
                         const RunContext &ctx);

@@ -125,12 +125,21 @@ extern "C" spmm_status spmm_submit(const spmm_work *items, int32_t count, void *
     std::vector<RunArgs> args(count);
     std::map<uint64_t, std::vector<int32_t>> groups;
     size_t ws_floats = 0;
+    auto window_items = [](const spmm_plan_t *p) { return (int64_t)p->dp.n_win + p->dp.n_wpart; };
+    int64_t win_items = 0;
+    for (int32_t i = 0; i < count; ++i)
+        if (items[i].plan->hp.m > 0) win_items += window_items(items[i].plan);
     for (int32_t i = 0; i < count; ++i) {
         const spmm_plan_t *p = items[i].plan;
         if (p->hp.m == 0) continue;
-        make_run_args(p, items[i].B, items[i].ldb, items[i].C, items[i].ldc, args[i]);
-        args[i].win_rows = 4;
-        args[i].win_subs = p->hp.opts.window_h / 16;  // the batched window kernels' waves take one 16-row block
+        make_run_args(p, items[i].B, items[i].ldb, items[i].C, items[i].ldc, args[i], win_items - window_items(p));
+        // The batched window kernels' waves take one 16-row block, or two of a
+        // 64-row window of 16-bit B where a single run's would take two or four,
+        // which load a B row half as often (bf16, 16 masks of 16,384 rows, N = 256:
+        // 1703 us, two blocks 838; 16 of 32,768 rows in blocks, N = 128: 489 / 290).
+        const int mb = p->hp.opts.window_h / 16;
+        const bool two = mb == 4 && args[i].win_subs <= 2 && args[i].win_np >= 64 && p->hp.b_type != SPMM_F32;
+        if (args[i].win_rows == 4) args[i].win_subs = two ? 2 : mb;
         ws_floats += workspace_floats(p->hp, true);
         const int E = args[i].vec_ok ? chunk_elems(p->hp.b_type) : 1;
         const int chunks = (args[i].np + E - 1) / E;
