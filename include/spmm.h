@@ -120,8 +120,8 @@ typedef struct {
                           class: a row of remainder length len is summed by S lane groups, S the
                           least power of two with len <= 2*U*S (at most all groups), entry p of
                           the row by group p mod S in entry order, then the groups' sums by an
-                          xor butterfly (classes 1 and all-groups sum as in variant 2; f32 B with N > 32
-                             not a multiple of 4 sums every row as variant 2 does); < 0: auto */
+                          xor butterfly (classes 1 and all-groups sum as in variant 2, and f32 B with
+                          N > 32 not a multiple of 4 has these two classes only); < 0: auto */
     int32_t win_sched; /* launch order of windows: 0 = by window id (neighbouring windows, which
                           tend to gather the same B rows, run together on one XCD); 1 = heaviest
                           first (LPT, Sec. 7 row-window lists); < 0: auto */

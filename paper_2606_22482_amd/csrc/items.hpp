@@ -1074,10 +1074,11 @@ __device__ __forceinline__ void vector_item_packed(const DevPlan &P, const RunAr
 }
 
 // Size class of a row: the least power of two S of lane groups with
-// len <= u2 * S, at most every group of the wavefront.
-__device__ __forceinline__ int size_class(int len, int u2, int groups) {
+// len <= u2 * S, at most every group of the wavefront (grow: log2 of the step
+// from one class to the next).
+__device__ __forceinline__ int size_class(int len, int u2, int groups, int grow) {
     int s = 1;
-    while (s < groups && len > u2 * s) s <<= 1;
+    while (s < groups && len > u2 * s) s <<= grow;
     return s;
 }
 
@@ -1114,6 +1115,11 @@ __device__ __forceinline__ void vector_item_classed(const DevPlan &P, const RunA
     chunk_layout<E, CPL>(ncol0, ncols, L, cok, coff);
     int sid = P.vitem_seg[item];
     const int i0 = P.vitem_ptr[item], i1 = P.vitem_ptr[item + 1];
+    // f32 rows of more than 32 columns that are not whole chunks are of class 1
+    // or all groups, which is the packed variant's order: at such widths the two
+    // variants give the same bits (as when a lane took one column of them, and a
+    // row of more than 32 all lanes).
+    const int grow = BT == DT_F32 && E > 1 && P.n > 32 && P.n % E != 0 ? 6 - L.lpr_log2 : 1;
     // id, remainder range, class and segments of rows base .. base + 63, one
     // per lane, loaded again only when fewer rows than a full pass takes
     // (L.groups) remain loaded
@@ -1132,7 +1138,7 @@ __device__ __forceinline__ void vector_item_classed(const DevPlan &P, const RunA
                     wns = (we - wb + P.seg_len - 1) / P.seg_len;
                     we = wb;  // the entries were summed by the segment kernel
                 } else {
-                    wcls = size_class(we - wb, 2 * unroll_of<E, CPL>(), L.groups);
+                    wcls = size_class(we - wb, 2 * unroll_of<E, CPL>(), L.groups, grow);
                 }
             }
         }
@@ -1226,12 +1232,14 @@ __device__ __forceinline__ void vector_item_classed(const DevPlan &P, const RunA
 // held entries cost one (f32 B 88 registers for 80: graph of 2^20 rows, N = 128,
 // 925 us, bounded 900; more spills: 997 and up) or, in the batch's 16-bit
 // kernel, two (64 uneven f16 matrices: 1086 us, bounded 1015).  Size classes
-// hold entries in the batch's half steps only (UL < 8); full steps need their 96
-// registers, and a bound of 80 spills 9 of them (f32, 200,000 rows, N = 128:
-// 202 us, unbounded 184).
+// hold entries in the batch's half steps only (UL < 8); full steps need 92 to 97
+// registers, of which 5 waves have 96, and a bound of 80 spills 9 of them (f32,
+// 200,000 rows, N = 128: 202 us, at 5 waves 184).
 template <int BT, int CPL, int VAR, int UL, bool HOLD>
 constexpr int vector_waves() {
-    if (CPL != 1 || VAR < 2 || !HOLD || (VAR == 3 && UL >= 8)) return 1;
+    if (CPL != 1 || VAR < 2) return 1;
+    if (VAR == 3 && UL >= 8) return 5;
+    if (!HOLD) return 1;
     return BT == DT_F32 ? 6 : UL < 8 ? 5 : 1;
 }
 

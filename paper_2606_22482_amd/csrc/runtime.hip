@@ -644,10 +644,7 @@ spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void
     a.cold_aux = (b_span < 4294967295.0 && al4 && h.opts.cold_policy != 0) ? h.opts.cold_policy : -1;
     // (a row of -1 has to wrap to an offset beyond the resource as well)
     a.b_rec = b_span + (double)ldb * sb < 4294967040.0 && al4 ? (uint32_t)b_span : 0u;
-    // f32 rows of more than 32 columns that are not whole chunks: size classes
-    // sum every row as the packed-row variant does (one order for both at such
-    // widths), and that variant is the faster one for f32 B
-    a.pipeline = h.opts.pipeline == 3 && sb == 4 && N % E != 0 && N > 32 ? 2 : h.opts.pipeline;
+    a.pipeline = h.opts.pipeline;
     // Entries held by the lanes that sum a row (or segment): rows of at least 16
     // lanes, and a run that gathers 300 MB or more.  Below, the entry loads hide
     // behind the waves' other latencies and the hand-out adds to them, and a row
