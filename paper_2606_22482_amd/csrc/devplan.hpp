@@ -26,7 +26,6 @@ struct DevPlan {
     const int32_t *seg_order;  // [n_seg] launch order of segments, or null for id order
     const int32_t *windows;    // [n_win*H]
     const int32_t *win_tile_ptr;  // [n_win+1]
-    const int32_t *win_seg;    // [n_win]
     const int32_t *win_order;  // [n_win], or null when windows run in id order
     const int32_t *tile_cols;  // [T*kt]
     const uint16_t *tile_dense;  // [(T+1)*H*kt] bf16 / f16 bits, row-major, zero where no entry is;
@@ -127,6 +126,9 @@ hipError_t launch_vector(const DevPlan &P, int32_t val_t, int32_t b_t, const Run
 // window owners, or (partial) the windows' partial items
 hipError_t launch_window(const DevPlan &P, int32_t val_t, int32_t b_t, int32_t tile_t,
                          const RunArgs &a, hipStream_t s, bool partial);
+// tiles from their bitmaps and packed values (row-major over set bits) to dense rows of 32
+hipError_t launch_spread_tiles(int64_t tiles, int32_t H, const uint32_t *bitmap, const int32_t *val_ptr,
+                               const uint16_t *vals, uint16_t *dense, hipStream_t s);
 hipError_t launch_copy(const float4 *src, float4 *dst, int64_t n4, hipStream_t s);
 
 // co-scheduled execution (fused.hip): the vector path (segments + vector

@@ -117,6 +117,26 @@ __global__ __launch_bounds__(256, 2) void batch_window_kernel(const BatchHeader 
     else SPMM_XCD_WALK(x_win, win_end, win_base, 4, (batch_window_item<VT, BT, TT, false>(tab[d], item)));
 }
 
+// One tile a wavefront (up to 64 rows of 32 slots): the rows' value counts are
+// summed over the lanes, then two rows a step are written side by side.
+__global__ __launch_bounds__(256) void spread_tiles_kernel(int64_t tiles, int32_t H, const uint32_t *__restrict__ bitmap,
+                                                           const int32_t *__restrict__ val_ptr,
+                                                           const uint16_t *__restrict__ vals,
+                                                           uint16_t *__restrict__ dense) {
+    const int64_t t = (int64_t)blockIdx.x * 4 + wave_id();
+    if (t >= tiles) return;
+    const int lane = threadIdx.x & 63;
+    const uint32_t w = lane < H ? bitmap[t * H + lane] : 0u;
+    const int before = wave_inclusive_scan(__popc(w)) - __popc(w);
+    const int64_t v0 = val_ptr[t];
+    for (int r0 = 0; r0 < H; r0 += 2) {
+        const int r = r0 + (lane >> 5), j = lane & 31;
+        const uint32_t m = (uint32_t)__shfl((int)w, r, 64);
+        const int64_t at = v0 + __shfl(before, r, 64) + __popc(m & ((1u << j) - 1u));
+        dense[(t * H + r) * 32 + j] = (m >> j) & 1u ? vals[at] : (uint16_t)0;
+    }
+}
+
 // Streaming copy used as the achievable-bandwidth reference: one 16-byte
 // load and store per lane per round over a large grid (measured on gfx950:
 // 5.4 TB/s read + write over 1 GiB; four loads in flight per lane over an
@@ -285,6 +305,15 @@ hipError_t launch_batch(const BatchHeader *hdr, const BatchEntry *tab, int32_t v
 hipError_t batch_occupancy(int32_t vt, int32_t bt, int32_t tt, int vec_ok, int cpl, int var,
                            BatchGrids *per_cu) {
     return batch_any(nullptr, nullptr, vt, bt, tt, vec_ok, cpl, var, BatchGrids{}, nullptr, per_cu);
+}
+
+hipError_t launch_spread_tiles(int64_t tiles, int32_t H, const uint32_t *bitmap, const int32_t *val_ptr,
+                               const uint16_t *vals, uint16_t *dense, hipStream_t s) {
+    if (tiles <= 0) return hipSuccess;
+    if (H < 2 || H > 64 || H % 2) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(spread_tiles_kernel, dim3(grid_for_waves(tiles)), dim3(256), 0, s, tiles, H, bitmap, val_ptr,
+                       vals, dense);
+    return hipGetLastError();
 }
 
 hipError_t launch_copy(const float4 *src, float4 *dst, int64_t n4, hipStream_t s) {

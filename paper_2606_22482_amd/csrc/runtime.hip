@@ -181,7 +181,6 @@ spmm_status upload_plan(spmm_plan_t *p, const DeviceArrays *da) {
         const size_t i_seg_end = add_vec(a, h.seg_end);
         const size_t i_windows = add_vec(a, h.windows);
         const size_t i_win_tile_ptr = add_vec(a, win_tile_ptr32);
-        const size_t i_win_seg = add_vec(a, h.win_seg);
         const size_t i_win_order = add_vec(a, h.win_order);
         // Launch order of the segments: by the column of each segment's middle
         // entry (stable).  A row's entries keep their CSR order, which is column
@@ -209,13 +208,16 @@ spmm_status upload_plan(spmm_plan_t *p, const DeviceArrays *da) {
         const size_t nt = h.tile_window.size();
         const size_t i_tile_cols = da ? a.add(da->tile_cols, 4 * nt * h.opts.kt, true) : add_vec(a, h.tile_cols);
         // The tiles' 16-bit values, dense: an MFMA operand is then one aligned
-        // load.  A plan's tiles hold at least alpha of their slots (1/16 by
-        // default), and a dense tile row is 64 bytes beside the 32 B rows that
-        // the tile gathers.
+        // load.  A tile is 64 bytes a row whatever it holds: at 16 rows 1 KiB, at
+        // 64 rows 4 KiB, beside the 32 B rows it gathers.  Its entries fill at
+        // least alpha (by default 1 / window_h) of its slots, so a plan takes up
+        // to 2 window_h bytes an entry of its tiles (with alpha 0, up to 64
+        // window_h), where a bitmap and packed values take 2 and 4 window_h a tile.
         // A tile of zeros follows them (odd numbers of tiles are padded with it).
-        const size_t slots = nt * (size_t)h.opts.window_h * h.opts.kt, pad = (size_t)h.opts.window_h * h.opts.kt;
-        const size_t i_tile_dense = a.add(da ? da->tile_dense : nullptr, 2 * slots, da != nullptr, 2 * pad);
-        const size_t i_tile_bitmap = a.add(da ? da->tile_bitmap : nullptr, da ? 4 * nt * h.opts.window_h : 0, true);
+        // A host plan's are spread on the device from the packed values.
+        const size_t H = (size_t)h.opts.window_h, slots = nt * H * h.opts.kt, pad = nt ? 2 * H * h.opts.kt : 16;
+        const size_t i_tile_dense = a.add(da ? da->tile_dense : nullptr, 2 * slots, nt > 0, pad);
+        const size_t i_tile_bitmap = da ? a.add(da->tile_bitmap, 4 * nt * H, true) : 0;
         const size_t i_win_part = add_vec(a, h.win_part);
         const size_t i_wpart_win = add_vec(a, h.wpart_win);
         const size_t i_wpart_t0 = add_vec(a, h.wpart_t0);
@@ -235,24 +237,44 @@ spmm_status upload_plan(spmm_plan_t *p, const DeviceArrays *da) {
             if (a.parts[i].second && !a.on_device[i] && a.parts[i].first)
                 std::memcpy(image.data() + a.offs[i], a.parts[i].first, a.parts[i].second);
 
-        if (!da) {
-            uint16_t *dense = reinterpret_cast<uint16_t *>(image.data() + a.offs[i_tile_dense]);
-            size_t v = 0;
-            for (size_t i = 0; i < h.tile_bitmap.size(); ++i)  // row-major over set bits
-                for (uint32_t w = h.tile_bitmap[i]; w; w &= w - 1) dense[i * 32 + __builtin_ctz(w)] = h.tile_vals[v++];
-        }
-
         int dev = 0;
         SPMM_TRY_HIP(hipGetDevice(&dev), "hipGetDevice");
         void *d = nullptr;
         hipError_t e = hipMalloc(&d, total);
         if (e != hipSuccess) return set_error(SPMM_ERR_OOM, std::string("hipMalloc(plan): ") + hipGetErrorString(e));
         e = hipMemcpy(d, image.data(), a.host, hipMemcpyHostToDevice);
-        if (e == hipSuccess && total > a.host) e = hipMemsetAsync(static_cast<uint8_t *>(d) + a.host, 0, total - a.host, 0);
-        for (size_t i = 0; i < a.parts.size() && e == hipSuccess; ++i)
-            if (a.parts[i].second && a.on_device[i])
-                e = hipMemcpy(static_cast<uint8_t *>(d) + a.offs[i], a.parts[i].first, a.parts[i].second,
-                              hipMemcpyDeviceToDevice);
+        for (size_t i = 0; i < a.parts.size() && e == hipSuccess; ++i) {
+            if (!a.on_device[i]) continue;
+            uint8_t *at = static_cast<uint8_t *>(d) + a.offs[i];
+            e = hipMemsetAsync(at + a.parts[i].second, 0, a.pads[i], nullptr);
+            if (e == hipSuccess && a.parts[i].second && a.parts[i].first)
+                e = hipMemcpy(at, a.parts[i].first, a.parts[i].second, hipMemcpyDeviceToDevice);
+        }
+        // a host plan's tiles: bitmaps, value offsets and packed values, spread
+        // by a kernel (the last two parts of a temporary block behind the bitmaps)
+        void *packed = nullptr;
+        if (!da && nt > 0 && e == hipSuccess) {
+            std::vector<int32_t> ptr(h.tile_val_ptr.begin(), h.tile_val_ptr.end());
+            const size_t nb = 4 * h.tile_bitmap.size(), np = 4 * ptr.size(), nv = 2 * h.tile_vals.size();
+            e = hipMalloc(&packed, nb + np + nv);
+            if (e != hipSuccess) {
+                (void)hipFree(d);
+                return set_error(SPMM_ERR_OOM, std::string("hipMalloc(tiles): ") + hipGetErrorString(e));
+            }
+            uint8_t *q = static_cast<uint8_t *>(packed);
+            e = hipMemcpy(q, h.tile_bitmap.data(), nb, hipMemcpyHostToDevice);
+            if (e == hipSuccess) e = hipMemcpy(q + nb, ptr.data(), np, hipMemcpyHostToDevice);
+            if (e == hipSuccess && nv) e = hipMemcpy(q + nb + np, h.tile_vals.data(), nv, hipMemcpyHostToDevice);
+            if (e == hipSuccess)
+                e = launch_spread_tiles((int64_t)nt, (int32_t)H, reinterpret_cast<const uint32_t *>(q),
+                                        reinterpret_cast<const int32_t *>(q + nb),
+                                        reinterpret_cast<const uint16_t *>(q + nb + np),
+                                        reinterpret_cast<uint16_t *>(static_cast<uint8_t *>(d) + a.offs[i_tile_dense]),
+                                        nullptr);
+        }
+        // (runs on other streams read the plan as soon as this returns)
+        if (e == hipSuccess && total > a.host) e = hipStreamSynchronize(nullptr);
+        if (packed) (void)hipFree(packed);
         if (e != hipSuccess) {
             (void)hipFree(d);
             return hip_error(e, "hipMemcpy(plan)");
@@ -279,7 +301,6 @@ spmm_status upload_plan(spmm_plan_t *p, const DeviceArrays *da) {
         dp.seg_order = seg_order.empty() ? nullptr : reinterpret_cast<const int32_t *>(at(i_seg_order));
         dp.windows = reinterpret_cast<const int32_t *>(at(i_windows));
         dp.win_tile_ptr = reinterpret_cast<const int32_t *>(at(i_win_tile_ptr));
-        dp.win_seg = reinterpret_cast<const int32_t *>(at(i_win_seg));
         bool order_id = true;
         for (size_t w = 0; w < h.win_order.size() && order_id; ++w) order_id = h.win_order[w] == (int32_t)w;
         dp.win_order = order_id ? nullptr : reinterpret_cast<const int32_t *>(at(i_win_order));
