@@ -112,7 +112,8 @@ typedef struct {
                             2 = nt, 16 = sc1, 18 = nt|sc1, 0 = default); < 0: auto (0: measured
                             fastest on gfx950).  Non-zero needs pipeline 0 (auto picks it) and
                             applies to the segment and vector kernels; window rows' remainders
-                            gather with the default policy. */
+                            gather with the default policy.  Rows of 16-bit B not aligned to 4
+                            bytes (an odd N, ldb or start) take its nt bit only. */
     int32_t pipeline;  /* vector kernel variant: 0 = row by row; 1 = prefetch the next row during
                           the current row's gathers (bitwise identical to 0); 2 = short rows (at
                           most two unrolled batches) packed one per lane group, each summed in

@@ -169,56 +169,6 @@ __device__ __forceinline__ uint32_t buf2(__amdgpu_buffer_rsrc_t rs, uint32_t off
 }
 
 template <int BT, int E>
-__device__ __forceinline__ void load_chunk_policy(__amdgpu_buffer_rsrc_t rs, int64_t off, int aux,
-                                                  float (&v)[E]) {
-    constexpr int SB = BT == DT_F32 ? 4 : 2;
-    const uint32_t boff = (uint32_t)(off * SB);
-    if constexpr (E == 1) {
-        uint32_t x;
-        if constexpr (SB == 4) {
-            switch (aux) {
-            case 2: x = buf4<2>(rs, boff); break;
-            case 16: x = buf4<16>(rs, boff); break;
-            case 18: x = buf4<18>(rs, boff); break;
-            default: x = buf4<0>(rs, boff); break;
-            }
-            v[0] = __uint_as_float(x);
-        } else {
-            switch (aux) {
-            case 2: x = buf2<2>(rs, boff); break;
-            case 16: x = buf2<16>(rs, boff); break;
-            case 18: x = buf2<18>(rs, boff); break;
-            default: x = buf2<0>(rs, boff); break;
-            }
-            v[0] = BT == DT_BF16 ? bf16_to_f32(x) : f16_to_f32(x);
-        }
-    } else {
-        u32x4 x;
-        switch (aux) {
-        case 2: x = buf16<2>(rs, boff); break;
-        case 16: x = buf16<16>(rs, boff); break;
-        case 18: x = buf16<18>(rs, boff); break;
-        default: x = buf16<0>(rs, boff); break;
-        }
-        if constexpr (BT == DT_F32) {
-            v[0] = __uint_as_float(x[0]); v[1] = __uint_as_float(x[1]);
-            v[2] = __uint_as_float(x[2]); v[3] = __uint_as_float(x[3]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if constexpr (BT == DT_BF16) {
-                    v[2 * i] = __uint_as_float(x[i] << 16);
-                    v[2 * i + 1] = __uint_as_float(x[i] & 0xFFFF0000u);
-                } else {
-                    v[2 * i] = f16_to_f32(x[i] & 0xFFFFu);
-                    v[2 * i + 1] = f16_to_f32(x[i] >> 16);
-                }
-            }
-        }
-    }
-}
-
-template <int BT, int E>
 __device__ __forceinline__ void load_raw_policy(__amdgpu_buffer_rsrc_t rs, int64_t off, int aux,
                                                 Raw<BT, E> &r) {
     constexpr int SB = BT == DT_F32 ? 4 : 2;
@@ -391,11 +341,13 @@ __device__ __forceinline__ void gather_fma(const int (&col)[U], const float (&v)
             // bit 31 of a column marks a hot B row (cacheable gather)
             const int64_t boff = (int64_t)(col[u] & 0x7FFFFFFF) * ldb + coff[c];
             if constexpr (POL) {
-                (void)brec;
                 if (ok && cok[c] && (col[u] < 0 || cold_aux < 0)) {
                     load_raw<BT, E, false>(B, boff, b[u][c]);
                 } else if (ok && cok[c]) {
-                    load_raw_policy<BT, E>(rs, boff, cold_aux, b[u][c]);
+                    // (rows not aligned to 4 bytes: plain loads, which know nt only)
+                    if (brec != 0) load_raw_policy<BT, E>(rs, boff, cold_aux, b[u][c]);
+                    else if (cold_aux & 2) load_raw<BT, E, true>(B, boff, b[u][c]);
+                    else load_raw<BT, E, false>(B, boff, b[u][c]);
                 } else {
                     zero_raw<BT, E>(b[u][c]);
                 }

@@ -662,7 +662,7 @@ spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void
     // and take chunks aligned to 4 bytes, which 16-bit rows of an odd N or
     // leading dimension are not
     const bool al4 = sb == 4 || (N % 2 == 0 && ldb % 2 == 0 && (uintptr_t)B % 4 == 0);
-    a.cold_aux = (b_span < 4294967295.0 && al4 && h.opts.cold_policy != 0) ? h.opts.cold_policy : -1;
+    a.cold_aux = (b_span < 4294967295.0 && h.opts.cold_policy != 0) ? h.opts.cold_policy : -1;
     // (a row of -1 has to wrap to an offset beyond the resource as well)
     a.b_rec = b_span + (double)ldb * sb < 4294967040.0 && al4 ? (uint32_t)b_span : 0u;
     a.pipeline = h.opts.pipeline;
