@@ -651,7 +651,9 @@ spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void
     int np = h.opts.n_panel > 0 ? std::min(h.opts.n_panel, N) : N;
     const int maxnp = a.vec_ok ? 128 * E : 128;
     np = std::min(np, maxnp);
-    if (a.vec_ok && np < N) np = std::max(E, np / E * E);
+    // a panel is whole chunks: the next fewer columns of N that are, else the next
+    // more, so that no panel is added to those of single columns
+    if (a.vec_ok && np < N) np = N % E == 0 ? std::max(E, np / E * E) : std::min(N, (np + E - 1) / E * E);
     a.np = np;
     a.n_panels = (N + np - 1) / np;
     const int chunks = a.vec_ok ? (np + E - 1) / E : np;
