@@ -14,8 +14,9 @@
  *                 a balanced list of work items (Sec. 7, row-window lists).
  *                 The plan is uploaded to the device once.
  *   spmm_run   -- one asynchronous execution on a HIP stream: MFMA over the
- *                 kept tiles, each B row loaded once a window, FP32 gather-FMA for the
- *                 remainder, one write of every C row.
+ *                 kept tiles, each B row loaded once for 16 to 64 rows of a
+ *                 window, FP32 gather-FMA for the remainder, one write of every
+ *                 C row.
  *
  * Conventions for every entry point:
  *   - Return value is an spmm_status; no C++ exception crosses the ABI.  On

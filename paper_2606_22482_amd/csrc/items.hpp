@@ -397,11 +397,12 @@ __device__ __forceinline__ void chunk_layout(int ncol0, int ncols, const Lanes &
 // those from the hold's first on (at clamped indices: a real entry of the row).
 // Two coalesced loads of each array serve as many steps as the hold spans,
 // where every lane loading its own group's entries takes 2 U loads a step, each
-// of one entry per group.  The vector path is bound by gathers in flight, and
-// the entry loads took half of its load slots (graphs, us, own loads / held:
-// 2^20 rows, N = 128 of f32 973 / 900; 500,000, N = 256 of bf16 568 / 492;
-// 200,003, N = 47 of f32 105 / 95; 64 uneven f16 matrices in a batch
-// 1192 / 1015).  Also loading the next hold or the next rows' entries ahead
+// of one entry per group.  A run whose gathers fill the card is bound by loads in
+// flight, and the entry loads took half of its load slots (graphs, us, own loads
+// / held: 2^20 rows, N = 128 of f32 956 / 884; 500,000, N = 256 of f16 558 / 479;
+// 200,000, N = 47 of f32 102 / 89; 64 uneven f16 matrices in a batch
+// 1183 / 1002).  Smaller and narrower runs get slower (the rule and both sides:
+// make_run_args).  Also loading the next hold or the next rows' entries ahead
 // costs registers and gained nothing (2^20 rows: 934 and 1052 us).
 struct Hold {
     int c[2];
@@ -1182,7 +1183,7 @@ __device__ __forceinline__ void vector_item_classed(const DevPlan &P, const RunA
 }
 // Waves per SIMD the kernels of vector items are compiled for, without which
 // held entries cost one (f32 B 88 registers for 80: graph of 2^20 rows, N = 128,
-// 925 us, bounded 900; more spills: 997 and up) or, in the batch's 16-bit
+// 925 us, bounded 891; more spills: 997 and up) or, in the batch's 16-bit
 // kernel, two (64 uneven f16 matrices: 1086 us, bounded 1015).  Size classes
 // hold entries in the batch's half steps only (UL < 8); full steps need 92 to 97
 // registers, of which 5 waves have 96, and a bound of 80 spills 9 of them (f32,
@@ -1297,9 +1298,10 @@ __device__ __forceinline__ int row16_broadcast(int x) {
 // Bound by B rows arriving from L2 and beyond (latency at small grids).  One
 // workgroup per (window, panel of 128) with B in LDS, a barrier per 4 tiles
 // and tile values expanded from the bitmap took (us, before / now): a 32,768-row attention mask
-// (H = 64) at N = 256 of bf16 230 / 114 (4.5 GB of B rows, 0.8 PFLOP/s with
+// (H = 64) at N = 256 of bf16 230 / 114 (1.0 GB of B rows, 0.57 PFLOP/s with
 // the tiles' zeros), 16,384 rows at N = 64 of f32 89 / 48, 3,001 rows at
-// N = 128 30 / 13; blocks of 262,144 rows (H = 16) at N = 256 of bf16 198 / 184.
+// N = 128 30 / 13; blocks of 262,144 rows (H = 16) at N = 256 of bf16 202 / 189.
+//
 // Waves per SIMD a kernel of window items is compiled for: 128 accumulators
 // (in AGPRs) leave room for one, a single block fits three.
 template <int MBW, int CW>

@@ -112,7 +112,7 @@ void resolve_options(const spmm_opts *in, const spmm_csr *A, int32_t n, int32_t 
     if (d.win_sched < 0) d.win_sched = 0;  // window id order: B rows reused in L2
     if (d.local_reorder < 0) d.local_reorder = 0;
     // co-scheduled as two concurrent grids (the vector path keeps its own
-    // occupancy beside the LDS-heavy windows); serial kernels for a cold
+    // occupancy beside the windows); serial kernels for a cold
     // policy, which only the serial kernels select per entry
     if (d.exec <= 0) d.exec = d.cold_policy != 0 ? 1 : 2;
     if (!(d.alpha_c >= 0.0f)) d.alpha_c = 1.0f / (float)d.window_h;

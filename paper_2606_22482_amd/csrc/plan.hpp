@@ -16,9 +16,10 @@ constexpr int kWave = 64;
 constexpr int kRowCost = 4;  // per-row overhead of a vector item, in entry units
 // Tiles a window item computes itself (the rest of a window's tiles go to
 // partial items of as many tiles each): the least power of two in
-// [kWinTiles, kWinTilesMax] that brings the plan's tiles over all 128-column
-// panels down to about kWindowItems items, i.e. about as many as the CUs
-// hold at once (window_item_tiles).  More, smaller items only add partial
+// [kWinTiles, kWinTilesMax] that brings the plan's tiles over panels of 128
+// columns down to about kWindowItems items, one for each SIMD of the card
+// (window_item_tiles; a run may take narrower panels, and more waves an item).
+// More, smaller items only add partial
 // results that go through memory and back (an item's partial C tile is as
 // large as its whole result).
 constexpr int kWinTiles = 16;

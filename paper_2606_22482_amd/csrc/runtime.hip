@@ -76,7 +76,7 @@ namespace {
 
 // Every sub-array is followed by at least 16 zero bytes, so a kernel that
 // clamps an index into [0, size] (an empty range included) stays inside the
-// allocation; the window kernel issues its predicated loads that way.
+// allocation; entries that lanes hold and window items' are loaded that way.
 // Parts from host memory first (one copy brings them), then those whose source
 // is device memory; 16 bytes of zeros (`pad`) or more behind each.
 struct Arena {
@@ -700,6 +700,8 @@ spmm_status make_run_args(const spmm_plan_t *p, const void *B, int64_t ldb, void
     a.win_rows = 4;
     const int mb = h.opts.window_h / 16;
     const int64_t items = (int64_t)p->dp.n_win + p->dp.n_wpart;
+    // (wanted waves, of the 1024 SIMDs: the four masks above and blocks are what
+    // was measured; between 94 and 750 waves a window of all its rows nothing)
     const int64_t want = p->dp.n_wpart > 0 ? 1100 : 700;
     auto waves = [&] { return (items + beside) * ((N + a.win_np - 1) / a.win_np) * a.win_subs; };
     // Windows that gather more B rows for their remainders than for their tiles
@@ -980,8 +982,8 @@ extern "C" spmm_status spmm_run_bytes(const spmm_plan_t *p, int64_t ldb, int64_t
     if (batched) {
         total += (double)workspace_floats(h, true) * 4.0;
     } else {
-        // the run's arguments with B and C aligned (the alignment decides the
-        // panel width and so the counters)
+        // the run's arguments with B and C aligned (which decides the panels of
+        // the vector path and so the counters)
         RunArgs a;
         make_run_args(p, reinterpret_cast<const void *>(256), ldb, reinterpret_cast<void *>(256), ldc, a);
         const bool serial = serial_exec(p, a);

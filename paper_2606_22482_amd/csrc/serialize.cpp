@@ -126,7 +126,8 @@ spmm_status check_plan(const HostPlan &P, std::string &err, int32_t *win_tiles) 
     SPMM_CHECK((int64_t)P.win_tile_ptr.size() == W + 1 && monotone_from_zero(P.win_tile_ptr, T),
                "plan image: window tiles");
     for (int64_t w = 0; w < W; ++w) {
-        // the window kernel takes its rows' metadata in its first tile round
+        // a window item loads its first tiles unasked, and its rows' first remainder
+        // entries in the place of the tile after the last
         SPMM_CHECK(P.win_tile_ptr[w + 1] > P.win_tile_ptr[w], "plan image: window without tiles");
         for (int32_t t = P.win_tile_ptr[w]; t < P.win_tile_ptr[w + 1]; ++t)
             SPMM_CHECK(P.tile_window[t] == w, "plan image: tile window");
@@ -151,7 +152,7 @@ spmm_status check_plan(const HostPlan &P, std::string &err, int32_t *win_tiles) 
             bits += __builtin_popcount(b);
         }
         SPMM_CHECK(bits == P.tile_val_ptr[t + 1] - P.tile_val_ptr[t], "plan image: tile value count");
-        // the window kernel reads a round's values at clamped indices
+        // (the builders keep no tile without entries)
         SPMM_CHECK(bits > 0, "plan image: tile without values");
     }
     // vector rows and items
